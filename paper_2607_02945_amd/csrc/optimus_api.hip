@@ -1380,13 +1380,13 @@ static optimus_status build_pointwise(const optimus_pointwise_desc* d, int32_t G
     // contiguous (ld == cols) and shorter than the wide row is re-viewed as
     // rows of kPwWideRow elements, so that every lane keeps several 16-byte
     // loads in flight instead of one per narrow row
-    int64_t rows = m.rows, cols = m.cols;
+    int64_t rows = m.rows, cols = m.cols, ldx = m.ldx, ldy = m.ldy;
     const int64_t total = m.rows * m.cols;
     if (m.ldx == m.cols && m.ldy == m.cols && m.cols < kPwWideRow && total % kPwWideRow == 0) {
       rows = total / kPwWideRow;
-      cols = kPwWideRow;
+      cols = ldx = ldy = kPwWideRow;
     }
-    members.push_back(make_rows(m.x, cols, m.y, cols, nullptr, nullptr, rows, cols, 0.f, dt, false));
+    members.push_back(make_rows(m.x, ldx, m.y, ldy, nullptr, nullptr, rows, cols, 0.f, dt, false));
     hp.bytes += (double)s * 2.0 * m.rows * m.cols;
   }
   build_rows(hp, members, false, s, act);

@@ -107,6 +107,19 @@ def test_grouped_pointwise(dtype, act):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_pointwise_strided_rows(dtype):
+    """Row strides wider than the rows, on both sides; nothing between the rows is written."""
+    say(f"[pointwise strided] {dtype}")
+    g = synth.rng(31)
+    for r, c, px, py in [(33, 24, 8, 0), (40, 64, 0, 16), (7, 13, 3, 2)]:
+        xb = dev(synth.to_storage(g.standard_normal((r, c + px)), dtype))
+        yb = torch.full((r, c + py), 77.0, dtype=xb.dtype, device="cuda")
+        B.optimus_grouped_pointwise([xb[:, :c]], [yb[:, :c]], "tanh")
+        assert_close(host64(yb[:, :c]), ORC.pointwise(host64(xb[:, :c]), "tanh"), dtype, f"{(r, c, px, py)}")
+        assert bool((yb[:, c:] == 77.0).all()), f"{(r, c, px, py)}: wrote beside its rows"
+
+
 def test_pointwise_saturation_and_special_values():
     say("[pointwise saturation]")
     v = torch.tensor([[-1e4, -100.0, -30.0, -1.0, -0.0, 0.0, 1.0, 30.0, 100.0, 1e4, 0.5, -0.5, 2.0, -2.0, 7.0, -7.0]],
