@@ -222,6 +222,37 @@ __device__ __forceinline__ void st16_nt(void* p, const u32x4& v) {
   __builtin_nontemporal_store(v, (OPTIMUS_GLOBAL u32x4*)p);
 }
 
+// The same 16 bytes at any element alignment (gfx950 global memory takes a
+// 16-byte access at any byte address; rows that start between two 16-byte
+// boundaries cost one more cache line per wave, not one access per value).
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+__device__ __forceinline__ u32x4 ld16u(const void* p) { return *(const OPTIMUS_GLOBAL u32x4_any*)p; }
+__device__ __forceinline__ void st16u(void* p, const u32x4& v) { *(OPTIMUS_GLOBAL u32x4_any*)p = v; }
+__device__ __forceinline__ u32x4 ld16u_nt(const void* p) {
+  return __builtin_nontemporal_load((const OPTIMUS_GLOBAL u32x4_any*)p);
+}
+__device__ __forceinline__ void st16u_nt(void* p, const u32x4& v) {
+  __builtin_nontemporal_store(v, (OPTIMUS_GLOBAL u32x4_any*)p);
+}
+
+// A chunk without its s lowest elements, zeros moved in at the top: what is
+// left of a row's last chunk when the 16 bytes that end at the row's end were
+// loaded for it (s = 0: the chunk itself).
+template <typename T>
+__device__ __forceinline__ u32x4 drop_low(const u32x4& v, int s) {
+  uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+  const int bits = s * (int)sizeof(T) * 8;
+  if (bits & 64) {
+    lo = hi;
+    hi = 0;
+  }
+  const int b = bits & 63;
+  lo = (lo >> b) | ((hi << 1) << (63 - b));
+  hi >>= b;
+  return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
 // ------------------------------------------------------------------ lane reductions
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {

@@ -23,20 +23,20 @@ __global__ __launch_bounds__(kRowThreads) void grouped_act_backward_kernel(const
     const RowTile rt = tiles[t];
     const DevRowsGrad d = descs[rt.member];
     const int end = rt.row0 + rt.nrows;
-    if (d.vec) {
+    {
       const int L = d.lanes, rpw = 64 / L, sub = lane / L, li = lane & (L - 1);
-      const int cpr = d.cols / VEC;
+      const int cpr = d.cols / VEC;  // whole chunks, at any alignment; then the values past them
       for (int r = rt.row0 + wave * rpw + sub; r < end; r += 4 * rpw) {
-        const char* xr = (const char*)d.x + (int64_t)r * d.ldx * sizeof(T);
-        const char* gr = (const char*)d.dy + (int64_t)r * d.lddy * sizeof(T);
-        char* orow = (char*)d.dx + (int64_t)r * d.lddx * sizeof(T);
+        const T* xr = (const T*)d.x + (int64_t)r * d.ldx;
+        const T* gr = (const T*)d.dy + (int64_t)r * d.lddy;
+        T* orow = (T*)d.dx + (int64_t)r * d.lddx;
         int c = li;
         for (; c + L < cpr; c += 2 * L) {
           u32x4 xv[2], gv[2];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            xv[u] = ld16_nt(xr + (int64_t)(c + u * L) * 16);
-            gv[u] = ld16_nt(gr + (int64_t)(c + u * L) * 16);
+            xv[u] = ld16u_nt(xr + (c + u * L) * VEC);
+            gv[u] = ld16u_nt(gr + (c + u * L) * VEC);
           }
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
@@ -45,23 +45,19 @@ __global__ __launch_bounds__(kRowThreads) void grouped_act_backward_kernel(const
             Elem<T>::unpack(gv[u], g);
 #pragma unroll
             for (int e = 0; e < VEC; ++e) a[e] = g[e] * act_grad<ACT>(a[e]);
-            st16_nt(orow + (int64_t)(c + u * L) * 16, Elem<T>::pack(a));
+            st16u_nt(orow + (c + u * L) * VEC, Elem<T>::pack(a));
           }
         }
         for (; c < cpr; c += L) {
           float a[VEC], g[VEC];
-          Elem<T>::unpack(ld16_nt(xr + (int64_t)c * 16), a);
-          Elem<T>::unpack(ld16_nt(gr + (int64_t)c * 16), g);
+          Elem<T>::unpack(ld16u_nt(xr + c * VEC), a);
+          Elem<T>::unpack(ld16u_nt(gr + c * VEC), g);
 #pragma unroll
           for (int e = 0; e < VEC; ++e) a[e] = g[e] * act_grad<ACT>(a[e]);
-          st16_nt(orow + (int64_t)c * 16, Elem<T>::pack(a));
+          st16u_nt(orow + c * VEC, Elem<T>::pack(a));
         }
-      }
-    } else {
-      for (int r = rt.row0 + wave; r < end; r += 4) {
-        const int64_t xo = (int64_t)r * d.ldx, go = (int64_t)r * d.lddy, oo = (int64_t)r * d.lddx;
-        for (int c = lane; c < d.cols; c += 64)
-          Elem<T>::store1(d.dx, oo + c, Elem<T>::load1(d.dy, go + c) * act_grad<ACT>(Elem<T>::load1(d.x, xo + c)));
+        for (int e = cpr * VEC + li; e < d.cols; e += L)
+          Elem<T>::store1(orow, e, Elem<T>::load1(gr, e) * act_grad<ACT>(Elem<T>::load1(xr, e)));
       }
     }
   }
@@ -83,7 +79,11 @@ __global__ __launch_bounds__(kRowThreads) void grouped_act_backward_kernel(const
 // the output pass reads them back (the derivative is two transcendentals per
 // value; large_group's LayerNorm + tanh backward 454 -> 413 us). Keeping
 // xhat there too saved nothing.
-template <typename T, int MAXC, int ACT>
+// RAG: rows of any width from VEC values on, at any alignment, as the forward
+// takes them: the chunk with a row's last values is the 16 bytes that end at
+// the row's end, its first `dup` values left out of every sum (gamma and beta
+// are staged chunk by chunk, the last one from the row's end too).
+template <typename T, int MAXC, int ACT, bool RAG>
 __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile& rt, int lane, int wave,
                                              float* sPart, const float* sGamma, const float* sBeta) {
   constexpr int VEC = Elem<T>::VEC;
@@ -91,7 +91,11 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
   const int rpw = 64 / L;
   const int sub = lane / L;
   const int li = lane & (L - 1);
-  const int cpr = d.cols / VEC;
+  const int cpr = RAG ? (d.cols + VEC - 1) / VEC : d.cols / VEC;
+  auto first_of = [&](int c) { return RAG ? min(c * VEC, d.cols - VEC) : c * VEC; };  // a chunk's first value
+  int dup[MAXC];
+#pragma unroll
+  for (int j = 0; j < MAXC; ++j) dup[j] = RAG ? (j * L + li) * VEC - first_of(j * L + li) : 0;
   const bool params = d.want_params != 0;
   auto param_of = [&](const float* src, int j, float (&gm)[VEC]) {
     const int c = j * L + li;
@@ -126,14 +130,14 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
   // computed (as the forward kernel does).
   u32x4 rx[MAXC], rg[MAXC];
   auto fetch = [&](int r) {
-    const char* xr = (const char*)d.x + (int64_t)r * d.ldx * sizeof(T);
-    const char* gr = (const char*)d.dy + (int64_t)r * d.lddy * sizeof(T);
+    const T* xr = (const T*)d.x + (int64_t)r * d.ldx;
+    const T* gr = (const T*)d.dy + (int64_t)r * d.lddy;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
       const int c = j * L + li;
       const bool in = r < end && c < cpr;
-      rx[j] = in ? ld16_nt(xr + (int64_t)c * 16) : u32x4{0u, 0u, 0u, 0u};
-      rg[j] = in ? ld16_nt(gr + (int64_t)c * 16) : u32x4{0u, 0u, 0u, 0u};
+      rx[j] = in ? ld16u_nt(xr + first_of(c)) : u32x4{0u, 0u, 0u, 0u};
+      rg[j] = in ? ld16u_nt(gr + first_of(c)) : u32x4{0u, 0u, 0u, 0u};
     }
   };
   fetch(rt.row0 + wave * rpw + sub);
@@ -157,7 +161,7 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
       float x[VEC];
       Elem<T>::unpack(cx[j], x);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) s += x[e];
+      for (int e = 0; e < VEC; ++e) s += !RAG || e >= dup[j] ? x[e] : 0.f;
     }
     const float mean = group_sum(s, L) * d.inv_cols;
     float q = 0.f;
@@ -169,7 +173,7 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
         const float t = x[e] - mean;
-        q += in ? t * t : 0.f;
+        q += in && (!RAG || e >= dup[j]) ? t * t : 0.f;
       }
     }
     const float rstd = __builtin_amdgcn_rsqf(group_sum(q, L) * d.inv_cols + d.eps);
@@ -193,13 +197,14 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
         const float gg = g[e] * gm[e];
-        sg += in ? gg : 0.f;
-        sgx += in ? gg * xh[e] : 0.f;
+        const bool ine = in && (!RAG || e >= dup[j]);
+        sg += ine ? gg : 0.f;
+        sgx += ine ? gg * xh[e] : 0.f;
       }
     }
     const float mg = group_sum(sg, L) * d.inv_cols;
     const float mgx = group_sum(sgx, L) * d.inv_cols;
-    char* orow = (char*)d.dx + (int64_t)r * d.lddx * sizeof(T);
+    T* orow = (T*)d.dx + (int64_t)r * d.lddx;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
       const int c = j * L + li;
@@ -227,7 +232,7 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
           accG[j][e] += g[e] * xh[e];
           accB[j][e] += g[e];
         }
-        st16_nt(orow + (int64_t)c * 16, Elem<T>::pack(o));
+        st16u_nt(orow + first_of(c), Elem<T>::pack(o));
       }
     }
   }
@@ -251,8 +256,9 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
         if (c < cpr) {
 #pragma unroll
           for (int e = 0; e < VEC; ++e) {
-            sPart[c * VEC + e] = accG[j][e];
-            sPart[d.cols + c * VEC + e] = accB[j][e];
+            if (RAG && e < dup[j]) continue;
+            sPart[first_of(c) + e] = accG[j][e];
+            sPart[d.cols + first_of(c) + e] = accB[j][e];
           }
         }
       }
@@ -339,11 +345,19 @@ __global__ __launch_bounds__(kRowThreads, 3) void grouped_layernorm_backward_ker
     const DevRowsGrad d = descs[rt.member];
     if (d.vec && d.lanes > 0) {
       const bool params = d.want_params != 0;
-      for (int i = tid; i < d.cols; i += kRowThreads) sGamma[i] = d.gamma ? Elem<T>::load1(d.gamma, i) : 1.f;
-      if constexpr (ACT != 0)
-        for (int i = tid; i < d.cols; i += kRowThreads) sBeta[i] = d.beta ? Elem<T>::load1(d.beta, i) : 0.f;
+      // chunk by chunk, the last chunk of a ragged row from the row's end
+      constexpr int VEC = Elem<T>::VEC;
+      const int whole = d.cols / VEC * VEC, staged = (d.cols + VEC - 1) / VEC * VEC;
+      for (int i = tid; i < staged; i += kRowThreads) {
+        const int c = i < whole ? i : d.cols - VEC + (i - whole);
+        sGamma[i] = d.gamma ? Elem<T>::load1(d.gamma, c) : 1.f;
+        if constexpr (ACT != 0) sBeta[i] = d.beta ? Elem<T>::load1(d.beta, c) : 0.f;
+      }
       __syncthreads();
-      lnb_rows_vec<T, kLnChunksPerLane, ACT>(d, rt, lane, wave, sPart[wave], sGamma, sBeta);
+      if (d.vec == 1)
+        lnb_rows_vec<T, kLnChunksPerLane, ACT, false>(d, rt, lane, wave, sPart[wave], sGamma, sBeta);
+      else
+        lnb_rows_vec<T, kLnChunksPerLane, ACT, true>(d, rt, lane, wave, sPart[wave], sGamma, sBeta);
       __syncthreads();  // every wave is done with sGamma and has written its slot
       if (params) {
         float* out = d.part + (int64_t)(d.part0 + rt.pad) * 2 * d.cols;

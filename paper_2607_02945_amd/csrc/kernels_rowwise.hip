@@ -21,14 +21,25 @@ constexpr int kLnDepth = 2;  // row slots loaded ahead of the one being computed
 // chunks of consecutive rows. Statistics are in fp32: mean first, then the
 // centred sum of squares over the row held in registers (two passes, no
 // cancellation), reduced across the L lanes with DPP / swizzle moves.
-template <typename T, int ACT, int MAXC>
+//
+// RAG: rows of any width from VEC values on, at any alignment. The chunk that
+// holds a row's last values is the 16 bytes that END at the row's end: its
+// first `dup` values belong to the chunk before it and are left out of the
+// statistics; both lanes compute and store the same results for them. (One
+// access per value and three passes, as such rows took before: 185 us on 48
+// bf16 members of 3001 rows of 20 to 500 values; this path 30 us, 5 TB/s.)
+template <typename T, int ACT, int MAXC, bool RAG>
 __device__ __forceinline__ void ln_rows_vec(const DevRows& d, const RowTile& rt, int lane, int wave) {
   constexpr int VEC = Elem<T>::VEC;
   const int L = d.lanes;
   const int rpw = 64 / L;
   const int sub = lane / L;
   const int li = lane & (L - 1);
-  const int cpr = d.cols / VEC;
+  const int cpr = RAG ? (d.cols + VEC - 1) / VEC : d.cols / VEC;
+  auto first_of = [&](int c) { return RAG ? min(c * VEC, d.cols - VEC) : c * VEC; };  // a chunk's first value
+  int dup[MAXC];
+#pragma unroll
+  for (int j = 0; j < MAXC; ++j) dup[j] = RAG ? (j * L + li) * VEC - first_of(j * L + li) : 0;
   // gamma / beta unpacked once per tile into fp32 registers; for sigmoid,
   // silu and tanh they also carry the activation's input scale
   // (act_scaled_in), so that the affine step yields the exponent's argument
@@ -39,13 +50,13 @@ __device__ __forceinline__ void ln_rows_vec(const DevRows& d, const RowTile& rt,
   for (int j = 0; j < MAXC; ++j) {
     const int c = j * L + li;
     if (d.gamma && c < cpr) {
-      Elem<T>::unpack(ld16((const char*)d.gamma + (int64_t)c * 16), gf[j]);
+      Elem<T>::unpack(ld16u((const T*)d.gamma + first_of(c)), gf[j]);
     } else {
 #pragma unroll
       for (int e = 0; e < VEC; ++e) gf[j][e] = 1.f;
     }
     if (d.beta && c < cpr) {
-      Elem<T>::unpack(ld16((const char*)d.beta + (int64_t)c * 16), bf[j]);
+      Elem<T>::unpack(ld16u((const T*)d.beta + first_of(c)), bf[j]);
     } else {
 #pragma unroll
       for (int e = 0; e < VEC; ++e) bf[j][e] = 0.f;
@@ -63,11 +74,11 @@ __device__ __forceinline__ void ln_rows_vec(const DevRows& d, const RowTile& rt,
   constexpr int PF = kLnDepth;
   u32x4 ring[PF][MAXC];
   auto fetch = [&](u32x4 (&dst)[MAXC], int r) {
-    const char* xr = (const char*)d.x + (int64_t)r * d.ldx * sizeof(T);
+    const T* xr = (const T*)d.x + (int64_t)r * d.ldx;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
       const int c = j * L + li;
-      dst[j] = (r < end && c < cpr) ? ld16_nt(xr + (int64_t)c * 16) : u32x4{0u, 0u, 0u, 0u};
+      dst[j] = (r < end && c < cpr) ? ld16u_nt(xr + first_of(c)) : u32x4{0u, 0u, 0u, 0u};
     }
   };
 #pragma unroll
@@ -87,7 +98,7 @@ __device__ __forceinline__ void ln_rows_vec(const DevRows& d, const RowTile& rt,
 #pragma unroll
     for (int j = 0; j < MAXC; ++j)
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) s += x[j][e];
+      for (int e = 0; e < VEC; ++e) s += !RAG || e >= dup[j] ? x[j][e] : 0.f;
     const float mean = group_sum(s, L) * d.inv_cols;
     float q = 0.f;
 #pragma unroll
@@ -96,11 +107,11 @@ __device__ __forceinline__ void ln_rows_vec(const DevRows& d, const RowTile& rt,
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
         x[j][e] -= mean;
-        q += in ? x[j][e] * x[j][e] : 0.f;
+        q += in && (!RAG || e >= dup[j]) ? x[j][e] * x[j][e] : 0.f;
       }
     }
     const float rstd = __builtin_amdgcn_rsqf(group_sum(q, L) * d.inv_cols + d.eps);
-    char* yr = (char*)d.y + (int64_t)r * d.ldy * sizeof(T);
+    T* yr = (T*)d.y + (int64_t)r * d.ldy;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
       const int c = j * L + li;
@@ -108,33 +119,58 @@ __device__ __forceinline__ void ln_rows_vec(const DevRows& d, const RowTile& rt,
         float o[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) o[e] = act_scaled_in<ACT>(x[j][e] * (rstd * gf[j][e]) + bf[j][e]);
-        st16_nt(yr + (int64_t)c * 16, Elem<T>::pack(o));
+        st16u_nt(yr + first_of(c), Elem<T>::pack(o));
       }
     }
   }
 }
 
-// Any shape, any alignment: one wave per row, three passes over global memory.
+// Any shape, any alignment: one wave per row, three passes over global memory
+// (the second and third read the row from cache), whole 16-byte chunks and
+// then the row's last cols % VEC values one per lane.
 template <typename T, int ACT>
-__device__ __forceinline__ void ln_rows_scalar(const DevRows& d, const RowTile& rt, int lane, int wave) {
+__device__ __forceinline__ void ln_rows_wide(const DevRows& d, const RowTile& rt, int lane, int wave) {
+  constexpr int VEC = Elem<T>::VEC;
   const int end = rt.row0 + rt.nrows;
+  const int cpr = d.cols / VEC, tail = cpr * VEC + lane;  // this lane's value past the whole chunks
+  const bool has_tail = tail < d.cols;
   for (int r = rt.row0 + wave; r < end; r += 4) {
-    const int64_t xo = (int64_t)r * d.ldx, yo = (int64_t)r * d.ldy;
-    float s = 0.f;
-    for (int c = lane; c < d.cols; c += 64) s += Elem<T>::load1(d.x, xo + c);
+    const T* xr = (const T*)d.x + (int64_t)r * d.ldx;
+    T* yr = (T*)d.y + (int64_t)r * d.ldy;
+    const float xt = has_tail ? Elem<T>::load1(xr, tail) : 0.f;
+    float s = xt;
+    for (int c = lane; c < cpr; c += 64) {
+      float v[VEC];
+      Elem<T>::unpack(ld16u(xr + c * VEC), v);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) s += v[e];
+    }
     const float mean = group_sum(s, 64) * d.inv_cols;
-    float q = 0.f;
-    for (int c = lane; c < d.cols; c += 64) {
-      const float t = Elem<T>::load1(d.x, xo + c) - mean;
-      q += t * t;
+    float q = has_tail ? (xt - mean) * (xt - mean) : 0.f;
+    for (int c = lane; c < cpr; c += 64) {
+      float v[VEC];
+      centred<T>(ld16u(xr + c * VEC), mean, v);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) q += v[e] * v[e];
     }
     const float rstd = __builtin_amdgcn_rsqf(group_sum(q, 64) * d.inv_cols + d.eps);
-    // All reads of this row are complete (the reductions above depend on
-    // them), so writing in place is safe.
-    for (int c = lane; c < d.cols; c += 64) {
-      const float gm = d.gamma ? Elem<T>::load1(d.gamma, c) : 1.f;
-      const float bt = d.beta ? Elem<T>::load1(d.beta, c) : 0.f;
-      Elem<T>::store1(d.y, yo + c, act_apply<ACT>((Elem<T>::load1(d.x, xo + c) - mean) * rstd * gm + bt));
+    // All reads of this row for the statistics are complete (the reductions
+    // above depend on them) and every value is now read again by the lane
+    // that writes it, so writing in place is safe.
+    for (int c = lane; c < cpr; c += 64) {
+      float v[VEC], gm[VEC], bt[VEC];
+      centred<T>(ld16u(xr + c * VEC), mean, v);
+      if (d.gamma) Elem<T>::unpack(ld16u((const T*)d.gamma + c * VEC), gm);
+      if (d.beta) Elem<T>::unpack(ld16u((const T*)d.beta + c * VEC), bt);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        v[e] = act_apply<ACT>(v[e] * rstd * (d.gamma ? gm[e] : 1.f) + (d.beta ? bt[e] : 0.f));
+      st16u_nt(yr + c * VEC, Elem<T>::pack(v));
+    }
+    if (has_tail) {
+      const float gm = d.gamma ? Elem<T>::load1(d.gamma, tail) : 1.f;
+      const float bt = d.beta ? Elem<T>::load1(d.beta, tail) : 0.f;
+      Elem<T>::store1(yr, tail, act_apply<ACT>((xt - mean) * rstd * gm + bt));
     }
   }
 }
@@ -147,10 +183,12 @@ __global__ __launch_bounds__(kRowThreads) void grouped_layernorm_kernel(const De
   for (int t = blockIdx.x; t < num_tiles; t += gridDim.x) {
     const RowTile rt = tiles[t];
     const DevRows d = descs[rt.member];
-    if (d.vec && d.lanes > 0)
-      ln_rows_vec<T, ACT, kLnChunksPerLane>(d, rt, lane, wave);
+    if (d.vec == 1)
+      ln_rows_vec<T, ACT, kLnChunksPerLane, false>(d, rt, lane, wave);
+    else if (d.vec == 2)
+      ln_rows_vec<T, ACT, kLnChunksPerLane, true>(d, rt, lane, wave);
     else
-      ln_rows_scalar<T, ACT>(d, rt, lane, wave);
+      ln_rows_wide<T, ACT>(d, rt, lane, wave);
   }
 }
 
@@ -169,39 +207,36 @@ __global__ __launch_bounds__(kRowThreads) void grouped_pointwise_kernel(const De
     const RowTile rt = tiles[t];
     const DevRows d = descs[rt.member];
     const int end = rt.row0 + rt.nrows;
-    if (d.vec) {
+    {
       const int L = d.lanes, rpw = 64 / L, sub = lane / L, li = lane & (L - 1);
       const int cpr = d.cols / VEC;
       for (int r = rt.row0 + wave * rpw + sub; r < end; r += 4 * rpw) {
-        const char* xr = (const char*)d.x + (int64_t)r * d.ldx * sizeof(T);
-        char* yr = (char*)d.y + (int64_t)r * d.ldy * sizeof(T);
-        // kPwInflight chunks per lane in flight, then the rest one at a time
+        const T* xr = (const T*)d.x + (int64_t)r * d.ldx;
+        T* yr = (T*)d.y + (int64_t)r * d.ldy;
+        // kPwInflight chunks per lane in flight, then the rest one at a time,
+        // then the row's last cols % VEC values
         int c = li;
         for (; c + (kPwInflight - 1) * L < cpr; c += kPwInflight * L) {
           u32x4 rv[kPwInflight];
 #pragma unroll
-          for (int u = 0; u < kPwInflight; ++u) rv[u] = ld16_nt(xr + (int64_t)(c + u * L) * 16);
+          for (int u = 0; u < kPwInflight; ++u) rv[u] = ld16u_nt(xr + (c + u * L) * VEC);
 #pragma unroll
           for (int u = 0; u < kPwInflight; ++u) {
             float v[VEC];
             Elem<T>::unpack(rv[u], v);
 #pragma unroll
             for (int e = 0; e < VEC; ++e) v[e] = act_apply<ACT>(v[e]);
-            st16_nt(yr + (int64_t)(c + u * L) * 16, Elem<T>::pack(v));
+            st16u_nt(yr + (c + u * L) * VEC, Elem<T>::pack(v));
           }
         }
         for (; c < cpr; c += L) {
           float v[VEC];
-          Elem<T>::unpack(ld16_nt(xr + (int64_t)c * 16), v);
+          Elem<T>::unpack(ld16u_nt(xr + c * VEC), v);
 #pragma unroll
           for (int e = 0; e < VEC; ++e) v[e] = act_apply<ACT>(v[e]);
-          st16_nt(yr + (int64_t)c * 16, Elem<T>::pack(v));
+          st16u_nt(yr + c * VEC, Elem<T>::pack(v));
         }
-      }
-    } else {
-      for (int r = rt.row0 + wave; r < end; r += 4) {
-        const int64_t xo = (int64_t)r * d.ldx, yo = (int64_t)r * d.ldy;
-        for (int c = lane; c < d.cols; c += 64) Elem<T>::store1(d.y, yo + c, act_apply<ACT>(Elem<T>::load1(d.x, xo + c)));
+        for (int e = cpr * VEC + li; e < d.cols; e += L) Elem<T>::store1(yr, e, act_apply<ACT>(Elem<T>::load1(xr, e)));
       }
     }
   }

@@ -532,7 +532,14 @@ static int pow2ceil(int v) {
   return p;
 }
 
-// Row-wise member: lanes per row and the 16-byte path.
+// Row-wise member: lanes per row and the kernel's path. All paths move 16
+// bytes per access: gfx950 takes them at any element alignment, so alignment
+// only decides how a row's end is handled.
+//   LayerNorm  vec 1: the row in registers, whole 16-byte aligned chunks;
+//              vec 2: in registers, any width from one chunk on and any
+//              alignment; vec 0: rows wider than the registers hold, or
+//              narrower than a chunk, in three passes
+//   pointwise  vec 1, whole chunks, then the values past them one per lane
 static DevRows make_rows(const void* x, int64_t ldx, void* y, int64_t ldy, const void* gamma, const void* beta,
                          int64_t rows, int64_t cols, float eps, optimus_dtype dt, bool layernorm) {
   const int VEC = dt == OPTIMUS_F32 ? 4 : 8;
@@ -542,22 +549,19 @@ static DevRows make_rows(const void* x, int64_t ldx, void* y, int64_t ldy, const
   r.rows = (int32_t)rows; r.cols = (int32_t)cols;
   r.eps = eps;
   r.inv_cols = (float)(1.0 / (double)cols);
-  const bool vec = cols % VEC == 0 && ldx % VEC == 0 && ldy % VEC == 0 && aligned16(x) && aligned16(y) &&
-                   (!gamma || aligned16(gamma)) && (!beta || aligned16(beta));
-  const int cpr = (int)(cols / VEC);
+  const int cpr = (int)((cols + VEC - 1) / VEC);
   r.vec = 0;
   r.lanes = 0;
-  if (vec) {
-    if (layernorm) {
-      const int maxc = kLnChunksPerLane;  // chunks per lane held in registers by the LayerNorm kernel
-      if (cpr <= 64 * maxc) {
-        r.vec = 1;
-        r.lanes = pow2ceil((cpr + maxc - 1) / maxc);
-      }
-    } else {
-      r.vec = 1;
-      r.lanes = std::min(64, pow2ceil(cpr));
+  if (layernorm) {
+    const bool whole = cols % VEC == 0 && ldx % VEC == 0 && ldy % VEC == 0 && aligned16(x) && aligned16(y);
+    const int maxc = kLnChunksPerLane;  // chunks per lane held in registers by the LayerNorm kernel
+    if (cols >= VEC && cpr <= 64 * maxc) {
+      r.vec = whole ? 1 : 2;
+      r.lanes = pow2ceil((cpr + maxc - 1) / maxc);
     }
+  } else {
+    r.vec = 1;
+    r.lanes = std::min(64, pow2ceil((int)std::max<int64_t>(cols / VEC, cols % VEC)));
   }
   return r;
 }
@@ -1165,8 +1169,7 @@ static optimus_status build_linear_backward(const optimus_linear_grad_desc* d, i
   return OPTIMUS_OK;
 }
 
-// Row-wise backward member: the forward's geometry (lanes per row, the
-// 16-byte path when x, dy, dx (and gamma) rows are 16-byte chunks).
+// Row-wise backward member: the forward's geometry (lanes per row and path).
 static DevRowsGrad make_rows_grad(const void* x, int64_t ldx, const void* dy, int64_t lddy, void* dx, int64_t lddx,
                                   const void* gamma, int64_t rows, int64_t cols, float eps, optimus_dtype dt,
                                   bool layernorm) {
@@ -1177,8 +1180,8 @@ static DevRowsGrad make_rows_grad(const void* x, int64_t ldx, const void* dy, in
   r.x = x; r.dy = dy; r.dx = dx; r.gamma = gamma;
   r.ldx = ldx; r.lddy = lddy; r.lddx = lddx;
   r.rows = (int32_t)rows; r.cols = (int32_t)cols;
-  r.vec = geo.vec && dy_ok ? 1 : 0;
-  r.lanes = r.vec ? geo.lanes : 0;
+  r.vec = geo.vec == 1 && layernorm && !dy_ok ? 2 : geo.vec;
+  r.lanes = geo.lanes;
   r.eps = eps;
   r.inv_cols = geo.inv_cols;
   return r;

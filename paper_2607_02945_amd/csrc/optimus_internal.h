@@ -79,8 +79,8 @@ struct DevRows {
   const void* beta;
   int64_t ldx, ldy;
   int32_t rows, cols;
-  int32_t lanes;   // lanes per row (power of two, 1..64) for the LayerNorm kernel
-  int32_t vec;     // 1 when rows are 16-B loadable/storable
+  int32_t lanes;   // lanes per row (power of two, 1..64), 0 on the LayerNorm kernel's three-pass path
+  int32_t vec;     // LayerNorm: 1 whole 16-B aligned chunks, 2 any width and alignment, 0 three passes
   float eps;
   float inv_cols;
 };

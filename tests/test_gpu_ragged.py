@@ -1,0 +1,95 @@
+"""Rows at any element alignment and of any width on the 16-byte paths: widths
+around the chunk, the lane group and the register path's limit, rows that
+start at an odd element, in place, and the values beside every row left as
+they are. Tolerances are those of the aligned paths (gpu_util)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2607_02945_amd import binding as B
+from paper_2607_02945_amd import synth
+from tests.gpu_util import assert_close, dev, host64, say
+
+pytestmark = pytest.mark.gpu
+ORC = oracle.get()
+# (rows, cols, elements before the row, after it): below, at and past one
+# chunk (8 bf16, 4 fp32), two lanes, a wave's lanes, the register path's last
+# width (1024 bf16, 512 fp32), and the three-pass path
+ROWS = [(7, 3, 1, 0), (65, 4, 0, 1), (33, 5, 1, 1), (130, 7, 0, 0), (19, 8, 1, 0), (21, 9, 0, 0), (40, 15, 3, 2),
+        (257, 17, 0, 0), (5, 129, 1, 0), (70, 511, 0, 0), (3, 513, 1, 2), (9, 1017, 0, 0), (6, 1023, 1, 1),
+        (4, 1024, 1, 0), (3, 1025, 0, 0), (2, 4099, 1, 0), (300, 64, 2, 0)]
+
+
+class Buf:
+    """A row-strided view whose surroundings hold a sentinel."""
+
+    def __init__(self, rows, cols, before, after, dtype, values=None):
+        self.base = torch.full((rows, before + cols + after), 77.0, dtype=synth.DTYPES[dtype], device="cuda")
+        self.view = self.base[:, before:before + cols]
+        self.span = (before, before + cols)
+        if values is not None:
+            self.view.copy_(dev(synth.to_storage(values, dtype)))
+
+    def surroundings_kept(self):
+        a, b = self.span
+        return bool((self.base[:, :a] == 77.0).all()) and bool((self.base[:, b:] == 77.0).all())
+
+
+def _bufs(dtype, seed, scale=1.0):
+    g = synth.rng(seed)
+    return [Buf(r, c, a, b, dtype, g.standard_normal((r, c)) * scale + 0.3) for r, c, a, b in ROWS]
+
+
+def _params(dtype, seed, mean):
+    g = synth.rng(seed)
+    # odd element offsets: gamma and beta are not 16-byte aligned either
+    return [dev(synth.to_storage(g.standard_normal(c + 1) * 0.3 + mean, dtype))[1:] for _, c, _, _ in ROWS]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_rowwise_forward(dtype, in_place):
+    say(f"[ragged rowwise] {dtype} in_place={in_place}")
+    gam, bet = _params(dtype, 1, 1.0), _params(dtype, 2, 0.0)
+    for op in ("layernorm", "pointwise"):
+        xs = _bufs(dtype, 3)
+        x64 = [host64(b.view) for b in xs]
+        ys = xs if in_place else [Buf(r, c, b, a, dtype) for r, c, a, b in ROWS]
+        xv, yv = [b.view for b in xs], [b.view for b in ys]
+        if op == "layernorm":
+            B.optimus_grouped_layernorm(xv, yv, gam, bet, 1e-5, "silu")
+        else:
+            B.optimus_grouped_pointwise(xv, yv, "tanh")
+        for i, (x, y) in enumerate(zip(x64, ys)):
+            ref = (ORC.layernorm(x, host64(gam[i]), host64(bet[i]), 1e-5, "silu") if op == "layernorm"
+                   else ORC.pointwise(x, "tanh"))
+            assert_close(host64(y.view), ref, dtype, f"{op} {ROWS[i]}")
+            assert y.surroundings_kept(), f"{op} {ROWS[i]}: wrote beside its rows"
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("act", ["none", "tanh"])
+def test_rowwise_backward(dtype, act):
+    say(f"[ragged rowwise backward] {dtype} {act}")
+    gam, bet = _params(dtype, 4, 1.0), _params(dtype, 5, 0.0)
+    xs, dys = _bufs(dtype, 6), _bufs(dtype, 7)
+    dxs = [Buf(r, c, b, a, dtype) for r, c, a, b in ROWS]
+    dgs, dbs = [torch.empty_like(g) for g in gam], [torch.empty_like(g) for g in gam]
+    xv, dyv, dxv = ([b.view for b in v] for v in (xs, dys, dxs))
+    B.optimus_grouped_layernorm_act_backward(xv, dyv, dxv, gam, bet, dgs, dbs, 1e-5, act)
+    for i, (x, dy, dx) in enumerate(zip(xv, dyv, dxs)):
+        x64, dy64, g64 = host64(x), host64(dy), host64(gam[i])
+        if act != "none":
+            dy64 = ORC.act_backward(ORC.layernorm(x64, g64, host64(bet[i]), 1e-5), dy64, act)
+        rdx, rdg, rdb = ORC.layernorm_backward(x64, g64, dy64, 1e-5)
+        assert_close(host64(dx.view), rdx, dtype, f"{ROWS[i]} dx")
+        assert_close(host64(dgs[i]), rdg, dtype, f"{ROWS[i]} dgamma")
+        assert_close(host64(dbs[i]), rdb, dtype, f"{ROWS[i]} dbeta")
+        assert dx.surroundings_kept(), f"{ROWS[i]}: wrote beside its rows"
+    # the activation backward alone, in place on dy
+    x64, dy64 = [host64(x) for x in xv], [host64(d) for d in dyv]
+    B.optimus_grouped_act_backward(xv, dyv, dyv, "silu")
+    for i, dy in enumerate(dys):
+        assert_close(host64(dy.view), ORC.act_backward(x64[i], dy64[i], "silu"), dtype, f"{ROWS[i]} act backward")
+        assert dy.surroundings_kept(), f"{ROWS[i]}: wrote beside its rows"
