@@ -16,6 +16,8 @@
 // past N and K past K_g are zero-filled on load and masked on store (the
 // in-kernel form of the pad -> matmul -> slice steps of the paper's pad_mm
 // case study, appendix Sec. 8.2, without materialising any padding).
+#include <algorithm>
+
 #include "device_common.h"
 
 namespace optimus {
@@ -77,24 +79,16 @@ struct GemmShape {
   static_assert((BM * BN / VEC) % NT == 0, "store phase must divide evenly");
 };
 
-// Load one 16-byte chunk of a K-contiguous operand row with zero fill past
-// the row count or past K. `vec` = rows are 16-byte aligned and K % VEC == 0.
+// One 16-byte chunk of a K-contiguous operand row, value by value, zero past
+// the row count or past K (rows shorter than a chunk).
 template <typename T>
-__device__ __forceinline__ u32x4 load_chunk(const void* base, int64_t ld, int row, int nrows, int k, int K, bool vec) {
+__device__ __forceinline__ u32x4 load_chunk_short(const void* base, int64_t ld, int row, int nrows, int k, int K) {
   constexpr int VEC = Elem<T>::VEC;
-  u32x4 v = {0u, 0u, 0u, 0u};
-  if (row < nrows && k < K) {
-    const T* p = (const T*)base + (int64_t)row * ld + k;
-    if (vec) {
-      v = ld16(p);
-    } else {
-      float f[VEC];
+  float f[VEC];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) f[e] = (k + e < K) ? Elem<T>::load1(p, e) : 0.f;
-      v = Elem<T>::pack(f);  // exact: the values are already representable in T
-    }
-  }
-  return v;
+  for (int e = 0; e < VEC; ++e)
+    f[e] = (row < nrows && k + e < K) ? Elem<T>::load1((const T*)base + (int64_t)row * ld, k + e) : 0.f;
+  return Elem<T>::pack(f);  // exact: the values are already representable in T
 }
 
 // ----------------------------------------------------------------- transposed operands
@@ -118,28 +112,6 @@ template <>
 struct Trans<float> {
   static constexpr int KB = 2;
 };
-
-// One 16-byte chunk of tile rows row..row+VEC-1 at reduction index k, zero
-// past nrows or K. `vec`: the chunk is 16-byte aligned (ld % VEC == 0 and an
-// aligned base).
-template <typename T>
-__device__ __forceinline__ u32x4 load_chunk_t(const void* base, int64_t ld, int row, int nrows, int k, int K,
-                                              bool vec) {
-  constexpr int VEC = Elem<T>::VEC;
-  u32x4 v = {0u, 0u, 0u, 0u};
-  if (k < K && row < nrows) {
-    const T* p = (const T*)base + (int64_t)k * ld + row;
-    if (vec && row + VEC <= nrows) {
-      v = ld16(p);
-    } else {
-      float f[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) f[e] = (row + e < nrows) ? Elem<T>::load1(p, e) : 0.f;
-      v = Elem<T>::pack(f);
-    }
-  }
-  return v;
-}
 
 // v[j]: reduction row k0 + j of the chunk; dst: LDS element (row0, k0) of the
 // [row][k] layout with row pitch LDK. Also adds each tile row's KB values to
@@ -352,7 +324,6 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16 (&acc)[BM / WM / 32][
     }
   }
   __syncthreads();
-  const bool vout = (d.vec & 2) != 0;
   constexpr int SCPR = BN / VEC;  // 16-byte pieces per staged row
   static_assert(NT % SCPR == 0 && (BM * SCPR) % NT == 0, "store phase must divide evenly");
   constexpr int RSTEP = NT / SCPR;  // rows covered per pass of the workgroup
@@ -362,8 +333,8 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16 (&acc)[BM / WM / 32][
   const int64_t ystep = (int64_t)RSTEP * d.ldy;
   if (n < Nr) {
     for (int row = r0; row < BM && row < Mr; row += RSTEP, sp += RSTEP * LDC, yp += ystep) {
-      if (vout && n + VEC <= Nr) {
-        st16(yp, *(const u32x4*)sp);
+      if (n + VEC <= Nr) {
+        st16u(yp, *(const u32x4*)sp);
       } else {
         for (int e = 0; e < VEC && n + e < Nr; ++e) {
           if constexpr (sizeof(T) == 2)
@@ -386,7 +357,17 @@ __device__ __forceinline__ void gemm_epilogue(const f32x16 (&acc)[BM / WM / 32][
 // (WM = 1, WN = 4) and a member no wider than half the tile, the two wave
 // pairs then take alternate K steps over the same columns and add their
 // partial sums through LDS before the epilogue (the tile's MFMA time halves).
-template <typename T, int BM, int BN, int BK, int WM, int WN, int STAGES, int ACT, int TR = 0, int PRE = 0>
+//
+// Operands at any alignment and of any width: every load is 16 bytes at a
+// clamped, valid address, with no branch between the loads of a step, and what
+// a clamped load brought too much of is dropped when the chunk goes to LDS. A
+// row's last, partial chunk is the 16 bytes that end at the row's end (nothing
+// past it is read), rows past the member's last repeat it (their outputs are
+// masked at the store; with a fused LayerNorm the weight rows are zeroed), and
+// steps past K store zeros. SHORT: some member has rows shorter than a chunk;
+// its K-contiguous (reduction-major) operands are read value by value.
+template <typename T, int BM, int BN, int BK, int WM, int WN, int STAGES, int ACT, int TR = 0, int PRE = 0,
+          bool SHORT = false>
 __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLinear* __restrict__ descs,
                                                                    const GemmTile* __restrict__ tiles,
                                                                    int32_t num_tiles) {
@@ -426,8 +407,6 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
     const DevLinear d = descs[tile.member];
     const int m0 = tile.mb * BM, n0 = tile.nb * BN;
     const int Mr = d.M - m0, Nr = d.N - n0;  // rows / columns left in this tile (may exceed BM / BN)
-    const bool vin = d.vec & 1;
-    const bool vw = TW ? (d.vec & 4) != 0 : vin;
     const T* xb = TX ? (const T*)d.x + m0 : (const T*)d.x + (int64_t)m0 * d.ldx;
     const T* wb = TW ? (const T*)d.w + n0 : (const T*)d.w + (int64_t)n0 * d.ldw;
     const bool want_sum = TX && d.xsum && tile.nb == 0;
@@ -454,38 +433,64 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     u32x4 rx[NRX], rw[NRW];
+    // K-contiguous operand: chunk idx of the step at k0 (row idx / CPR)
+    auto load_n = [&](const T* base, int64_t ld, int idx, int nrows, int k0) {
+      const int row = idx / CPR, k = k0 + idx % CPR * VEC;
+      if constexpr (SHORT) return load_chunk_short<T>(base, ld, row, nrows, k, kend);
+      return ld16u(base + (int64_t)min(row, nrows - 1) * ld + min(k, kend - VEC));
+    };
+    auto keep_n = [&](u32x4 v, int idx, int nrows, int k0, bool zero_rows) {
+      if (!SHORT && k0 + BK > kend) {
+        const int k = k0 + idx % CPR * VEC, drop = k - (kend - VEC);
+        if (drop > 0) v = k < kend ? drop_low<T>(v, drop) : u32x4{0u, 0u, 0u, 0u};
+      }
+      if (!SHORT && zero_rows && idx / CPR >= nrows) v = u32x4{0u, 0u, 0u, 0u};
+      return v;
+    };
+    // reduction-major operand: rows rg * VEC .. + VEC - 1 at reduction index k
+    auto load_t = [&](const T* base, int64_t ld, int rg, int nrows, int k) {
+      if constexpr (SHORT) {
+        float f[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+          f[e] = (k < kend && rg * VEC + e < nrows) ? Elem<T>::load1(base + (int64_t)k * ld, rg * VEC + e) : 0.f;
+        return Elem<T>::pack(f);
+      }
+      return ld16u(base + (int64_t)min(k, kend - 1) * ld + min(rg * VEC, nrows - VEC));
+    };
+    auto keep_t = [&](u32x4 v, int rg, int nrows, int k) {
+      if (SHORT) return v;
+      const int drop = rg * VEC - (nrows - VEC);
+      if (drop > 0 && drop < VEC) v = drop_low<T>(v, drop);
+      return k < kend ? v : u32x4{0u, 0u, 0u, 0u};
+    };
     auto gload_to = [&](u32x4 (&ox)[NRX], u32x4 (&ow)[NRW], int k0) {
       if constexpr (TX) {
 #pragma unroll
         for (int i = 0; i < LXT; ++i) {
           const int idx = tid + i * NT, kq = idx % (BK / KB), rg = idx / (BK / KB);
 #pragma unroll
-          for (int j = 0; j < KB; ++j) ox[i * KB + j] = load_chunk_t<T>(xb, d.ldx, rg * VEC, Mr, k0 + kq * KB + j, kend, vin);
+          for (int j = 0; j < KB; ++j) ox[i * KB + j] = load_t(xb, d.ldx, rg, Mr, k0 + kq * KB + j);
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < S::LX; ++i) {
-          const int idx = tid + i * NT, row = idx / CPR, c = idx % CPR;
-          ox[i] = load_chunk<T>(xb, d.ldx, row, Mr, k0 + c * VEC, kend, vin);
-        }
+        for (int i = 0; i < S::LX; ++i) ox[i] = load_n(xb, d.ldx, tid + i * NT, Mr, k0);
       }
       if constexpr (TW) {
 #pragma unroll
         for (int i = 0; i < LWT; ++i) {
           const int idx = tid + i * NT, kq = idx % (BK / KB), rg = idx / (BK / KB);
 #pragma unroll
-          for (int j = 0; j < KB; ++j) ow[i * KB + j] = load_chunk_t<T>(wb, d.ldw, rg * VEC, Nr, k0 + kq * KB + j, kend, vw);
+          for (int j = 0; j < KB; ++j) ow[i * KB + j] = load_t(wb, d.ldw, rg, Nr, k0 + kq * KB + j);
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < S::LW; ++i) {
-          const int idx = tid + i * NT, row = idx / CPR, c = idx % CPR;
-          ow[i] = load_chunk<T>(wb, d.ldw, row, Nr, k0 + c * VEC, kend, vin);
-        }
+        for (int i = 0; i < S::LW; ++i) ow[i] = load_n(wb, d.ldw, tid + i * NT, Nr, k0);
       }
     };
     auto gload = [&](int k0) { gload_to(rx, rw, k0); };
-    auto lstore_from = [&](const u32x4 (&rx)[NRX], const u32x4 (&rw)[NRW], int stage) {
+    // k0: the step the registers hold
+    auto lstore_from = [&](const u32x4 (&rx)[NRX], const u32x4 (&rw)[NRW], int stage, int k0) {
       T* sx = sAB + stage * S::STAGE_ELEMS;
       T* sw = sx + BM * LDK;
       if constexpr (TX) {
@@ -494,14 +499,14 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
           const int idx = tid + i * NT, kq = idx % (BK / KB), rg = idx / (BK / KB);
           u32x4 blk[KB];
 #pragma unroll
-          for (int j = 0; j < KB; ++j) blk[j] = rx[i * KB + j];
+          for (int j = 0; j < KB; ++j) blk[j] = keep_t(rx[i * KB + j], rg, Mr, k0 + kq * KB + j);
           store_trans(blk, sx + rg * VEC * LDK + kq * KB, LDK, want_sum, xs[i]);
         }
       } else {
 #pragma unroll
         for (int i = 0; i < S::LX; ++i) {
           const int idx = tid + i * NT, row = idx / CPR, c = idx % CPR;
-          *(u32x4*)(sx + row * LDK + c * VEC) = rx[i];
+          *(u32x4*)(sx + row * LDK + c * VEC) = keep_n(rx[i], idx, Mr, k0, false);
         }
       }
       if constexpr (TW) {
@@ -511,18 +516,18 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
           const int idx = tid + i * NT, kq = idx % (BK / KB), rg = idx / (BK / KB);
           u32x4 blk[KB];
 #pragma unroll
-          for (int j = 0; j < KB; ++j) blk[j] = rw[i * KB + j];
+          for (int j = 0; j < KB; ++j) blk[j] = keep_t(rw[i * KB + j], rg, Nr, k0 + kq * KB + j);
           store_trans(blk, sw + rg * VEC * LDK + kq * KB, LDK, false, unused);
         }
       } else {
 #pragma unroll
         for (int i = 0; i < S::LW; ++i) {
           const int idx = tid + i * NT, row = idx / CPR, c = idx % CPR;
-          *(u32x4*)(sw + row * LDK + c * VEC) = rw[i];
+          *(u32x4*)(sw + row * LDK + c * VEC) = keep_n(rw[i], idx, Nr, k0, LN);
         }
       }
     };
-    auto lstore = [&](int stage) { lstore_from(rx, rw, stage); };
+    auto lstore = [&](int stage, int k0) { lstore_from(rx, rw, stage, k0); };
     // MFMA over one staged step; wcol: the wave's column block (wn, or the
     // block it shares under the K split)
     auto compute = [&](int stage, int wcol) {
@@ -562,8 +567,8 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
 #pragma unroll
           for (int s = 0; s < PRE; s += 2) {
             if (s < nk) {
-              lstore_from(px[s], pw[s], 0);
-              if (s + 1 < nk) lstore_from(px[s + 1], pw[s + 1], 1);
+              lstore_from(px[s], pw[s], 0, kbeg + s * BK);
+              if (s + 1 < nk) lstore_from(px[s + 1], pw[s + 1], 1, kbeg + (s + 1) * BK);
               __syncthreads();
               if (s + pair < nk) compute(pair, wn & 1);
               __syncthreads();
@@ -594,13 +599,13 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
           }
           __syncthreads();  // hand-over read before the epilogue stages into the same area
         } else {
-          lstore_from(px[0], pw[0], 0);
+          lstore_from(px[0], pw[0], 0, kbeg);
           __syncthreads();
 #pragma unroll
           for (int s = 0; s < PRE; ++s) {
             if (s < nk) {
               compute(s & 1, wn);
-              if (s + 1 < nk) lstore_from(px[s + 1], pw[s + 1], (s + 1) & 1);
+              if (s + 1 < nk) lstore_from(px[s + 1], pw[s + 1], (s + 1) & 1, kbeg + (s + 1) * BK);
               __syncthreads();
             }
           }
@@ -611,19 +616,19 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
     } else if constexpr (STAGES == 2) {
       gload(kbeg);
       load_col_params<T, BN, LN>(sBias, sGamma, sBeta, d, n0, Nr);
-      lstore(0);
+      lstore(0, kbeg);
       __syncthreads();
       for (int kb = 0; kb < nk; ++kb) {
         if (kb + 1 < nk) gload(kbeg + (kb + 1) * BK);
         compute(kb & 1, wn);
-        if (kb + 1 < nk) lstore((kb + 1) & 1);
+        if (kb + 1 < nk) lstore((kb + 1) & 1, kbeg + (kb + 1) * BK);
         __syncthreads();
       }
     } else {
       for (int kb = 0; kb < nk; ++kb) {
         gload(kbeg + kb * BK);
         if (kb == 0) load_col_params<T, BN, LN>(sBias, sGamma, sBeta, d, n0, Nr);
-        lstore(0);
+        lstore(0, kbeg + kb * BK);
         __syncthreads();
         compute(0, wn);
         __syncthreads();
@@ -658,7 +663,6 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
         // fp32 partial tile straight from the accumulators: each lane holds
         // four consecutive columns of one row per (i, j, quad)
         float* wb = d.ws + ((int64_t)tile.pad * d.M + m0) * d.N + n0;
-        const bool v4 = (d.N & 3) == 0;
 #pragma unroll
         for (int i = 0; i < S::FM; ++i) {
           const int row = wm * S::TM + i * 32 + l32;
@@ -669,8 +673,8 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
             for (int q = 0; q < 4; ++q) {
               const int col = wn * S::TN + j * 32 + 8 * q + 4 * lh;
               float* p = wb + (int64_t)row * d.N + col;
-              if (v4 && col + 3 < Nr) {
-                *(OPTIMUS_GLOBAL f32x4*)p = f32x4{acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
+              if (col + 3 < Nr) {
+                *(OPTIMUS_GLOBAL f32x4_any*)p = f32x4{acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
                                                  acc[i][j][q * 4 + 3]};
               } else {
 #pragma unroll
@@ -716,6 +720,26 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
 // instructions ahead of the first MFMA).
 constexpr int kR16Rows = 16, kR16Cols = 128, kR16Batch = 8;
 
+// Four consecutive k of a row, zero past the row count or past K; `whole`:
+// K % 4 == 0. A row's last, partial chunk is read value by value (dropping
+// elements in registers, as the register-staged tiles do, cost 5 % here: the
+// launch is short enough for its code size to count).
+__device__ __forceinline__ u32x4 r16_chunk(const float* base, int64_t ld, int row, int nrows, int k, int K, bool whole) {
+  u32x4 v = {0u, 0u, 0u, 0u};
+  if (row < nrows && k < K) {
+    const float* p = base + (int64_t)row * ld + k;
+    if (whole || k + 4 <= K) {
+      v = ld16u(p);
+    } else {
+      float f[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] = (k + e < K) ? Elem<float>::load1(p, e) : 0.f;
+      v = Elem<float>::pack(f);
+    }
+  }
+  return v;
+}
+
 template <int ACTX>
 __global__ __launch_bounds__(256) void grouped_gemm_rows16_kernel(const DevLinear* __restrict__ descs,
                                                                  const GemmTile* __restrict__ tiles,
@@ -757,9 +781,9 @@ __global__ __launch_bounds__(256) void grouped_gemm_rows16_kernel(const DevLinea
       for (int i = 0; i < KB; ++i) {
         if (g0 + i < g_end) {
           const int k = (g0 + i) * 16 + lq * 4;
-          b[i][0] = load_chunk<float>(wb, d.ldw, l16, wrows, k, d.K, vin);
-          b[i][1] = load_chunk<float>(wb, d.ldw, 16 + l16, wrows, k, d.K, vin);
-          b[i][2] = load_chunk<float>(xb, d.ldx, l16, Mr, k, d.K, vin);
+          b[i][0] = r16_chunk(wb, d.ldw, l16, wrows, k, d.K, vin);
+          b[i][1] = r16_chunk(wb, d.ldw, 16 + l16, wrows, k, d.K, vin);
+          b[i][2] = r16_chunk(xb, d.ldx, l16, Mr, k, d.K, vin);
         }
       }
     };
@@ -878,15 +902,14 @@ __global__ __launch_bounds__(256) void grouped_gemm_rows16_kernel(const DevLinea
     }
     if (sk == 0 && l16 < Mr) {
       float* yr = (float*)d.y + (int64_t)(m0 + l16) * d.ldy + n0;
-      const bool vout = (d.vec & 2) != 0;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int c = cl + 16 * j;
         float v[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = act_apply<ACT>(o[j][r]);
-        if (vout && c + 3 < Nr) {
-          st16(yr + c, __builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}));
+        if (c + 3 < Nr) {
+          st16u(yr + c, __builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}));
         } else {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
@@ -1311,7 +1334,6 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_dma_kernel(const Dev
         // fp32 partial tile straight from the accumulators: each lane holds
         // four consecutive columns of one row per (i, j, quad)
         float* wb = d.ws + ((int64_t)tile.pad * d.M + m0) * d.N + n0;
-        const bool v4 = (d.N & 3) == 0;
 #pragma unroll
         for (int i = 0; i < S::FM; ++i) {
           const int row = wm * S::TM + i * 32 + l32;
@@ -1322,8 +1344,8 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_dma_kernel(const Dev
             for (int q = 0; q < 4; ++q) {
               const int col = wn * S::TN + j * 32 + 8 * q + 4 * lh;
               float* p = wb + (int64_t)row * d.N + col;
-              if (v4 && col + 3 < Nr) {
-                *(OPTIMUS_GLOBAL f32x4*)p = f32x4{acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
+              if (col + 3 < Nr) {
+                *(OPTIMUS_GLOBAL f32x4_any*)p = f32x4{acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
                                                  acc[i][j][q * 4 + 3]};
               } else {
 #pragma unroll
@@ -1354,7 +1376,7 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_dma_kernel(const Dev
       const char* wget = wst + lrow * S::PITCH + lc * 16;
       const float* bput = sBias + wcol0 + (lane_o >> 5) * 4;
       const int tc = wcol0 + lc * 8;  // tile column of this lane's stores
-      const bool col_in = tc < Nr, col_vec = (d.vec & 2) != 0 && tc + 8 <= Nr;
+      const bool col_in = tc < Nr, col_vec = tc + 8 <= Nr;
       bf16_t* ybase = (bf16_t*)d.y + (int64_t)(m0 + wrow0) * d.ldy + n0 + tc + (int64_t)lrow * d.ldy;
       const bf16_t* abase = nullptr;
       if constexpr (AG != 0) abase = (const bf16_t*)d.ax + (int64_t)(m0 + wrow0 + lrow) * d.ldax + n0 + tc;
@@ -1376,8 +1398,8 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_dma_kernel(const Dev
 #pragma unroll
           for (int r = 0; r < S::HR / RPP; ++r) {
             const int lim = Mr - (wrow0 + h * S::HR + r * RPP);
-            av[r] = (lrow < lim && col_vec && (d.vec & 8))
-                        ? ld16_nt(abase + (int64_t)(h * S::HR + r * RPP) * d.ldax)
+            av[r] = (lrow < lim && col_vec)
+                        ? ld16u_nt(abase + (int64_t)(h * S::HR + r * RPP) * d.ldax)
                         : u32x4{0u, 0u, 0u, 0u};
           }
         }
@@ -1412,13 +1434,13 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_dma_kernel(const Dev
               // dX * act'(ax): the stored value times the derivative at the
               // activation's input, rounded once more to bf16
               const bf16_t* ap = abase + (int64_t)(h * S::HR + r * RPP) * d.ldax;
-              if (col_vec && (d.vec & 8)) {
+              if (col_vec) {
                 float g[8], a[8];
                 Elem<bf16_t>::unpack(v, g);
                 Elem<bf16_t>::unpack(av[r], a);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) g[e] *= act_grad<AG>(a[e]);
-                st16_nt(yp, Elem<bf16_t>::pack(g));
+                st16u_nt(yp, Elem<bf16_t>::pack(g));
               } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
@@ -1429,7 +1451,7 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_dma_kernel(const Dev
                   }
               }
             } else if (col_vec) {
-              st16_nt(yp, v);  // y is not read again by this launch
+              st16u_nt(yp, v);  // y is not read again by this launch
             } else {
 #pragma unroll
               for (int e = 0; e < 8; ++e)
@@ -2009,9 +2031,10 @@ bool gemm_dma_wt_ok(const optimus_linear_desc* d, int32_t G) {
 int gemm_ln_max_n(optimus_dtype dt) { return dt == OPTIMUS_F32 ? 128 : 256; }
 
 GemmConfig gemm_pick_config(optimus_dtype dt, const optimus_linear_desc* d, int32_t G, bool ln, int pin) {
-  int64_t maxN = 0, maxK = 0;
+  int64_t maxN = 0, maxK = 0, minK = INT32_MAX;
   double tiles256 = 0.0;
   for (int g = 0; g < G; ++g) {
+    minK = d[g].K < minK ? d[g].K : minK;
     maxN = d[g].N > maxN ? d[g].N : maxN;
     maxK = d[g].K > maxK ? d[g].K : maxK;
     tiles256 += (double)((d[g].M + 255) / 256) * (double)((d[g].N + 255) / 256);
@@ -2049,6 +2072,22 @@ GemmConfig gemm_pick_config(optimus_dtype dt, const optimus_linear_desc* d, int3
     if (tiles32 < device_cu_count() && maxK <= 1024) v = 10;
   } else if (maxN <= 64 && maxK <= 64) {
     v = (!ln && gemm_stream_ok(d, G)) ? 9 : 0;
+  } else if (!dma && !ln) {
+    // rows at any alignment, register-staged: the narrow tile wastes least of
+    // its columns on members of a few hundred and spreads small groups over
+    // the CUs; groups of wide members gain from the larger tiles' reuse. Us
+    // on 128x64 / 128x128 / 256x256 (members x rows; K, N ranges): 8 x 257
+    // 15 / 18 / 34, 48 x 4001 (33-300, 20-250) 46 / 50 / 62, 24 x 4001
+    // (33-700, 20-500) 70 / 73 / 71, 48 x 3001 (same) 108 / 103 / 99, 12 x 4001
+    // (401-999, 256-900) 123 / 104 / 108, 16 x 8001 (same) 343 / 260 / 224
+    double area = 0.0, rows = 0.0, tiles128 = 0.0;
+    for (int g = 0; g < G; ++g) {
+      area += (double)d[g].M * (double)d[g].N;
+      rows += (double)d[g].M;
+      tiles128 += (double)((d[g].M + 127) / 128) * (double)((d[g].N + 127) / 128);
+    }
+    const double cus = device_cu_count();
+    v = tiles256 >= 3.0 * cus && area > 192.0 * rows ? 2 : area > 384.0 * rows && tiles128 >= cus ? 1 : 0;
   } else if (tiles256 >= 0.5 * device_cu_count() || (ln && maxN > 128)) {
     // measured over groups of 64 to 4096 256x256 tiles: the 256x256 tile wins
     // from half a tile per CU on (and is the one that holds rows past 128)
@@ -2058,7 +2097,7 @@ GemmConfig gemm_pick_config(optimus_dtype dt, const optimus_linear_desc* d, int3
     v = dma ? 5 : 1;
   }
   const GemmVariant& k = kVariants[v];
-  return GemmConfig{k.bm, k.bn, v, k.threads, k.occ, k.name};
+  return GemmConfig{k.bm, k.bn, v, k.threads, k.occ, k.name, minK < (dt == OPTIMUS_F32 ? 4 : 8)};
 }
 
 // Workgroups of one kernel instance that fit on a CU at once (registers, LDS).
@@ -2115,12 +2154,16 @@ static hipError_t launch_skinny(optimus_act act, const DevLinear* descs, const G
 }
 
 template <typename T, int BM, int BN, int BK, int WM, int WN, int STAGES, int PRE = 0>
-static hipError_t launch_shape(optimus_act act, bool ln, const DevLinear* descs, const GemmTile* tiles, int32_t n,
+static hipError_t launch_shape(optimus_act act, bool ln, bool shrt, const DevLinear* descs, const GemmTile* tiles, int32_t n,
                                int32_t grid, hipStream_t stream, int* occ) {
   using S = GemmShape<T, BM, BN, BK, WM, WN, STAGES>;
 #define OPTIMUS_GEMM_LAUNCH(A)                                                                                   \
-  if (ln)                                                                                                        \
+  if (ln && shrt)                                                                                                \
+    OPTIMUS_LAUNCH_ONE((grouped_gemm_kernel<T, BM, BN, BK, WM, WN, STAGES, (A) | 8, 0, 0, true>), S::LDS_BYTES_LN, S::NT) \
+  else if (ln)                                                                                                   \
     OPTIMUS_LAUNCH_ONE((grouped_gemm_kernel<T, BM, BN, BK, WM, WN, STAGES, (A) | 8, 0, PRE>), S::LDS_BYTES_LN, S::NT) \
+  else if (shrt)                                                                                                 \
+    OPTIMUS_LAUNCH_ONE((grouped_gemm_kernel<T, BM, BN, BK, WM, WN, STAGES, (A), 0, 0, true>), S::LDS_BYTES, S::NT) \
   else                                                                                                           \
     OPTIMUS_LAUNCH_ONE((grouped_gemm_kernel<T, BM, BN, BK, WM, WN, STAGES, (A), 0, PRE>), S::LDS_BYTES, S::NT)
   switch (act) {
@@ -2156,10 +2199,12 @@ static hipError_t launch_rows16(optimus_act act, bool ln, const DevLinear* descs
 
 // Backward GEMM instances: no bias, no activation, no LayerNorm.
 template <typename T, int BM, int BN, int BK, int WM, int WN, int STAGES>
-static hipError_t launch_trans(int tr, const DevLinear* descs, const GemmTile* tiles, int32_t n, int32_t grid,
+static hipError_t launch_trans(int tr, bool shrt, const DevLinear* descs, const GemmTile* tiles, int32_t n, int32_t grid,
                                hipStream_t stream, int* occ) {
   using S = GemmShape<T, BM, BN, BK, WM, WN, STAGES>;
-  if (tr == 3)
+  if (tr == 3 && shrt)
+    OPTIMUS_LAUNCH_ONE((grouped_gemm_kernel<T, BM, BN, BK, WM, WN, STAGES, 0, 3, 0, true>), S::LDS_BYTES, S::NT)
+  else if (tr == 3)
     OPTIMUS_LAUNCH_ONE((grouped_gemm_kernel<T, BM, BN, BK, WM, WN, STAGES, 0, 3>), S::LDS_BYTES, S::NT)
   else
     return hipErrorInvalidValue;
@@ -2214,24 +2259,24 @@ static hipError_t gemm_dispatch(const GemmConfig& cfg, optimus_dtype dt, optimus
   if (tr) {
     if (ln || (act != OPTIMUS_ACT_NONE && tr != 2)) return hipErrorInvalidValue;
     switch (cfg.variant) {
-      case 1: return launch_trans<bf16_t, 128, 128, 64, 2, 2, 2>(tr, descs, tiles, n, grid, stream, occ);
-      case 2: return launch_trans<bf16_t, 256, 256, 64, 2, 4, 2>(tr, descs, tiles, n, grid, stream, occ);
-      case 3: return launch_trans<float, 64, 64, 32, 2, 2, 2>(tr, descs, tiles, n, grid, stream, occ);
+      case 1: return launch_trans<bf16_t, 128, 128, 64, 2, 2, 2>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
+      case 2: return launch_trans<bf16_t, 256, 256, 64, 2, 4, 2>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
+      case 3: return launch_trans<float, 64, 64, 32, 2, 2, 2>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
       case 4: return launch_dma_trans<256, 256, 2, 4>(tr, act, descs, tiles, n, grid, stream, occ);
       case 5: return launch_dma_trans<128, 128, 2, 2>(tr, act, descs, tiles, n, grid, stream, occ);
-      case 6: return launch_trans<float, 64, 128, 64, 2, 2, 2>(tr, descs, tiles, n, grid, stream, occ);
+      case 6: return launch_trans<float, 64, 128, 64, 2, 2, 2>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
       default: return hipErrorInvalidValue;
     }
   }
   switch (cfg.variant) {
-    case 0: return launch_shape<bf16_t, 128, 64, 64, 4, 1, 1>(act, ln, descs, tiles, n, grid, stream, occ);
-    case 1: return launch_shape<bf16_t, 128, 128, 64, 2, 2, 2>(act, ln, descs, tiles, n, grid, stream, occ);
-    case 2: return launch_shape<bf16_t, 256, 256, 64, 2, 4, 2>(act, ln, descs, tiles, n, grid, stream, occ);
-    case 3: return launch_shape<float, 64, 64, 32, 2, 2, 2>(act, ln, descs, tiles, n, grid, stream, occ);
+    case 0: return launch_shape<bf16_t, 128, 64, 64, 4, 1, 1>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
+    case 1: return launch_shape<bf16_t, 128, 128, 64, 2, 2, 2>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
+    case 2: return launch_shape<bf16_t, 256, 256, 64, 2, 4, 2>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
+    case 3: return launch_shape<float, 64, 64, 32, 2, 2, 2>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
     case 4: return launch_dma<256, 256, 2, 4>(act, ln, descs, tiles, n, grid, stream, occ);
     case 5: return launch_dma<128, 128, 2, 2>(act, ln, descs, tiles, n, grid, stream, occ);
-    case 6: return launch_shape<float, 64, 128, 64, 2, 2, 2>(act, ln, descs, tiles, n, grid, stream, occ);
-    case 8: return launch_shape<float, 32, 128, 64, 1, 4, 2, 4>(act, ln, descs, tiles, n, grid, stream, occ);
+    case 6: return launch_shape<float, 64, 128, 64, 2, 2, 2>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
+    case 8: return launch_shape<float, 32, 128, 64, 1, 4, 2, 4>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
     case 10:
       if (dt != OPTIMUS_F32) return hipErrorInvalidValue;
       return launch_rows16(act, ln, descs, tiles, n, grid, stream, occ);
@@ -2258,7 +2303,9 @@ hipError_t gemm_launch(const GemmConfig& cfg, optimus_dtype dt, optimus_act act,
 GemmConfig gemm_pick_config_trans(optimus_dtype dt, const optimus_linear_desc* d, int32_t G, bool split_k, int tile,
                                   int pin) {
   double tiles256 = 0.0, area = 0.0;
+  int64_t minw = INT32_MAX;  // the narrowest row of either operand
   for (int g = 0; g < G; ++g) {
+    minw = std::min({minw, d[g].M, d[g].N});
     tiles256 += (double)((d[g].M + 255) / 256) * (double)((d[g].N + 255) / 256);
     area += (double)d[g].M * (double)d[g].N;
   }
@@ -2281,7 +2328,7 @@ GemmConfig gemm_pick_config_trans(optimus_dtype dt, const optimus_linear_desc* d
     v = dt == OPTIMUS_F32 ? 3 : big ? (dma ? 4 : 2) : (dma ? 5 : 1);
   }
   const GemmVariant& k = kVariants[v];
-  return GemmConfig{k.bm, k.bn, v, k.threads, k.occ, k.name};
+  return GemmConfig{k.bm, k.bn, v, k.threads, k.occ, k.name, minw < (dt == OPTIMUS_F32 ? 4 : 8)};
 }
 
 int gemm_resident_per_cu(const GemmConfig& cfg, optimus_dtype dt, optimus_act act, bool ln, int tr) {

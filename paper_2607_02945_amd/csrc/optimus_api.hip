@@ -732,7 +732,16 @@ static void build_gemm_set(HostPlan& hp, GemmSet& gs, const GemmConfig& cfg, int
     a = b;
   }
   gs.real_tiles = (int64_t)tiles.size();
-  const int64_t cap = (int64_t)device_cu_count() * gemm_resident_per_cu(cfg, hp.dt, act, ln, tr);
+  // The fp32 64-row tiles carry nothing from one tile to the next and run
+  // several workgroups per CU: each tile gets its own workgroup, and the
+  // hardware refills a CU as soon as one ends (16 members of 2048 rows, K and N
+  // of 64 to 512: 84 us against 100 for a persistent grid, whose second round
+  // leaves most of the matrix cores idle). The bf16 register-staged tiles
+  // were slower that way (103 -> 109 us, 260 -> 296). kDeal consecutive tiles,
+  // which share an x panel, go to one XCD, the next kDeal to the next one.
+  const bool one_each = cfg.variant == 3 || cfg.variant == 6;
+  const int64_t cap = one_each ? (int64_t)1 << 30
+                               : (int64_t)device_cu_count() * gemm_resident_per_cu(cfg, hp.dt, act, ln, tr);
   // The kernels hand XCD x (the hardware deals workgroups round-robin to the
   // 8 XCDs) the items at positions r * grid + x * grid / 8 + [0, grid / 8) of
   // round r. Over more than one round, each XCD gets one contiguous eighth of
@@ -749,7 +758,18 @@ static void build_gemm_set(HostPlan& hp, GemmSet& gs, const GemmConfig& cfg, int
     bool one_k = true;
     for (const DevLinear& dd : descs) one_k = one_k && dd.K == descs[0].K;
     // (the tiled kernels; the skinny kernel walks items in plain order, the streaming kernel below)
-    if (tr == 0 && one_k && g >= 8 && T > g && cfg.variant != 7 && cfg.variant != 9) {
+    constexpr int64_t kDeal = 8;
+    if (one_each && T >= 16 * kDeal) {
+      const int64_t per = (T + 8 * kDeal - 1) / (8 * kDeal) * kDeal;  // positions per XCD
+      std::vector<GemmTile> dealt_tiles((size_t)(8 * per), GemmTile{-1, 0, 0, 0});
+      for (int64_t i = 0; i < T; ++i) {
+        const int64_t round = i / (8 * kDeal), x = i / kDeal % 8;
+        dealt_tiles[(size_t)(x * per + round * kDeal + i % kDeal)] = tiles[(size_t)i];
+      }
+      tiles.swap(dealt_tiles);
+      reordered = true;
+    }
+    if (tr == 0 && one_k && g >= 8 && T > g && !one_each && cfg.variant != 7 && cfg.variant != 9) {
       const int64_t per = g / 8, chunk = (T + 7) / 8, rounds = (chunk + per - 1) / per;
       std::vector<GemmTile> dealt_tiles((size_t)(rounds * g), GemmTile{-1, 0, 0, 0});
       for (int64_t x = 0; x < 8; ++x)
@@ -968,9 +988,10 @@ static optimus_status build_linear_backward(const optimus_linear_grad_desc* d, i
       DevLinear o{};
       o.x = m.dy; o.ldx = m.lddy; o.w = m.x; o.ldw = m.ldx; o.y = m.dw; o.ldy = m.lddw; o.xsum = m.db;
       o.M = (int32_t)m.N; o.N = (int32_t)m.K; o.K = (int32_t)m.M;
-      const bool vx = m.lddy % VEC == 0 && aligned16(m.dy);
+      // aligned rows of whole chunks, as the reduction-major loads see them
+      const bool vx = m.N % VEC == 0 && m.lddy % VEC == 0 && aligned16(m.dy);
       const bool vout = m.lddw % VEC == 0 && aligned16(m.dw);
-      const bool vw = m.ldx % VEC == 0 && aligned16(m.x);
+      const bool vw = m.K % VEC == 0 && m.ldx % VEC == 0 && aligned16(m.x);
       o.vec = (vx ? 1 : 0) | (vout ? 2 : 0) | (vw ? 4 : 0);
       o.inv_n = 1.0f / (float)m.K;
       dws.push_back(o);

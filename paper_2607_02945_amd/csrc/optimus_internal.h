@@ -121,6 +121,7 @@ struct GemmConfig {
   int threads;
   int occ;             // workgroups resident per CU
   const char* name;
+  bool shrt = false;   // some member's operand rows are shorter than 16 bytes (the register-staged instances)
 };
 
 // ln: the group's LayerNorm is fused into the epilogue, so one tile must hold

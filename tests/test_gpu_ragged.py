@@ -93,3 +93,55 @@ def test_rowwise_backward(dtype, act):
     for i, dy in enumerate(dys):
         assert_close(host64(dy.view), ORC.act_backward(x64[i], dy64[i], "silu"), dtype, f"{ROWS[i]} act backward")
         assert dy.surroundings_kept(), f"{ROWS[i]}: wrote beside its rows"
+
+
+# (M, N, K): one chunk and less, around the 16-byte chunk, the K step and the
+# tile edges of every register-staged kernel
+LINEAR = [(5, 3, 7), (33, 9, 8), (64, 17, 9), (130, 65, 63), (257, 129, 65), (70, 255, 127), (129, 257, 129),
+          (300, 66, 201), (513, 31, 515)]
+
+
+def _linear_bufs(dtype, seed):
+    g = synth.rng(seed)
+    ms = []
+    for i, (M, N, K) in enumerate(LINEAR):
+        x = Buf(M, K, i % 3, i % 2, dtype, g.standard_normal((M, K)))
+        w = Buf(N, K, (i + 1) % 3, 0, dtype, g.standard_normal((N, K)) / np.sqrt(K))
+        b = dev(synth.to_storage(g.standard_normal(N) * 0.1, dtype))
+        dy = Buf(M, N, i % 2, i % 3, dtype, g.standard_normal((M, N)))
+        ms.append((x, w, b, dy))
+    return ms
+
+
+@pytest.mark.parametrize("dtype,tile", [("bf16", 1), ("bf16", 2), ("bf16", 3), ("fp32", 4), ("fp32", 7), ("fp32", 9),
+                                        ("fp32", 11)])
+def test_linear_forward(dtype, tile):
+    say(f"[ragged linear] {dtype} tile={tile}")
+    ms = _linear_bufs(dtype, 8)
+    ys = [Buf(M, N, (i + 1) % 2, i % 3, dtype) for i, (M, N, K) in enumerate(LINEAR)]
+    p = B.optimus_plan_linear_ex([m[0].view for m in ms], [m[1].view for m in ms], [m[2] for m in ms],
+                                 [y.view for y in ys], "relu", {"gemm_tile": tile})
+    p.execute()
+    for i, ((x, w, b, _), y) in enumerate(zip(ms, ys)):
+        ref = ORC.linear(host64(x.view), host64(w.view), host64(b), "relu")
+        assert_close(host64(y.view), ref, dtype, f"tile {tile} {LINEAR[i]}")
+        assert y.surroundings_kept(), f"tile {tile} {LINEAR[i]}: wrote beside its rows"
+
+
+@pytest.mark.parametrize("dtype,tile,splits", [("bf16", 0, 0), ("bf16", 2, 1), ("bf16", 3, 0), ("fp32", 0, 0),
+                                               ("fp32", 7, 1)])
+def test_linear_backward(dtype, tile, splits):
+    say(f"[ragged linear backward] {dtype} tile={tile} splits={splits}")
+    ms = _linear_bufs(dtype, 9)
+    dxs = [Buf(M, K, i % 2, 1, dtype) for i, (M, N, K) in enumerate(LINEAR)]
+    dws = [Buf(N, K, 0, i % 2, dtype) for i, (M, N, K) in enumerate(LINEAR)]
+    dbs = [torch.empty_like(m[2]) for m in ms]
+    p = B.optimus_plan_linear_backward_ex([m[0].view for m in ms], [m[1].view for m in ms], [m[3].view for m in ms],
+                                          [b.view for b in dxs], [b.view for b in dws], dbs,
+                                          {"gemm_tile": tile, "wgrad_splits": splits})
+    p.execute()
+    for i, (x, w, _, dy) in enumerate(ms):
+        rdx, rdw, rdb = ORC.linear_backward(host64(x.view), host64(w.view), host64(dy.view))
+        for what, got, ref in (("dx", dxs[i].view, rdx), ("dw", dws[i].view, rdw), ("db", dbs[i], rdb)):
+            assert_close(host64(got), ref, dtype, f"tile {tile} {LINEAR[i]} {what}")
+        assert dxs[i].surroundings_kept() and dws[i].surroundings_kept(), f"{LINEAR[i]}: wrote beside its rows"
