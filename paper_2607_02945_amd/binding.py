@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import List, Optional, Sequence
 
 import torch
@@ -229,10 +230,13 @@ def _act(a) -> int:
 
 
 def _mat(t: torch.Tensor, name: str):
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
-        raise ValueError(f"{name}: need a 2-D tensor with unit inner stride, got shape {tuple(t.shape)} "
-                         f"strides {t.stride()}")
-    return t.data_ptr(), max(t.stride(0), t.shape[1])
+    shape = t.shape
+    strides = t.stride()
+    if len(shape) != 2 or (strides[1] != 1 and shape[1] > 1):
+        raise ValueError(f"{name}: need a 2-D tensor with unit inner stride, got shape {tuple(shape)} "
+                         f"strides {strides}")
+    ld, cols = strides[0], shape[1]
+    return t.data_ptr(), ld if ld > cols else cols
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -245,38 +249,52 @@ def _stream(stream) -> Optional[int]:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+def _packed(desc, fields: int, vals: list, G: int) -> ctypes.Array:
+    """G descriptors of `fields` 8-byte words each, from one flat list of their
+    values in declaration order (one ctypes conversion for the whole group: a
+    structure per member costs more than its tensors' own accessors)."""
+    words = (c_i64 * (fields * max(G, 1)))(*vals)
+    return (desc * max(G, 1)).from_buffer(words)
+
+
 def linear_descs(xs, ws, biases, ys) -> ctypes.Array:
-    G = len(xs)
-    arr = (LinearDesc * max(G, 1))()
-    for g in range(G):
-        x, ldx = _mat(xs[g], "x")
-        w, ldw = _mat(ws[g], "w")
-        y, ldy = _mat(ys[g], "y")
-        arr[g] = LinearDesc(x, ldx, w, ldw, _ptr(biases[g] if biases is not None else None), y, ldy,
-                            xs[g].shape[0], ws[g].shape[0], xs[g].shape[1])
-    return arr
+    vals = []
+    for g, (x, w, y) in enumerate(zip(xs, ws, ys)):
+        xp, ldx = _mat(x, "x")
+        wp, ldw = _mat(w, "w")
+        yp, ldy = _mat(y, "y")
+        M, K = x.shape
+        b = biases[g] if biases is not None else None
+        vals += (xp, ldx, wp, ldw, 0 if b is None else b.data_ptr(), yp, ldy, M, w.shape[0], K)
+    return _packed(LinearDesc, 10, vals, len(xs))
+
+
+def _f32_word(v: float) -> int:
+    """The 8-byte word whose low half is the float v (a structure's last field, padded)."""
+    return int.from_bytes(struct.pack("<f", float(v)), "little")
 
 
 def layernorm_descs(xs, ys, gammas, betas, eps) -> ctypes.Array:
-    G = len(xs)
-    arr = (LayerNormDesc * max(G, 1))()
-    for g in range(G):
-        x, ldx = _mat(xs[g], "x")
-        y, ldy = _mat(ys[g], "y")
-        arr[g] = LayerNormDesc(x, ldx, y, ldy, _ptr(gammas[g] if gammas is not None else None),
-                               _ptr(betas[g] if betas is not None else None), xs[g].shape[0], xs[g].shape[1],
-                               float(eps))
-    return arr
+    vals = []
+    e = _f32_word(eps)
+    for g, (x, y) in enumerate(zip(xs, ys)):
+        xp, ldx = _mat(x, "x")
+        yp, ldy = _mat(y, "y")
+        gm = gammas[g] if gammas is not None else None
+        bt = betas[g] if betas is not None else None
+        rows, cols = x.shape
+        vals += (xp, ldx, yp, ldy, 0 if gm is None else gm.data_ptr(), 0 if bt is None else bt.data_ptr(), rows, cols, e)
+    return _packed(LayerNormDesc, 9, vals, len(xs))
 
 
 def pointwise_descs(xs, ys) -> ctypes.Array:
-    G = len(xs)
-    arr = (PointwiseDesc * max(G, 1))()
-    for g in range(G):
-        x, ldx = _mat(xs[g], "x")
-        y, ldy = _mat(ys[g], "y")
-        arr[g] = PointwiseDesc(x, ldx, y, ldy, xs[g].shape[0], xs[g].shape[1])
-    return arr
+    vals = []
+    for x, y in zip(xs, ys):
+        xp, ldx = _mat(x, "x")
+        yp, ldy = _mat(y, "y")
+        rows, cols = x.shape
+        vals += (xp, ldx, yp, ldy, rows, cols)
+    return _packed(PointwiseDesc, 6, vals, len(xs))
 
 
 def _opt_mat(t, name):

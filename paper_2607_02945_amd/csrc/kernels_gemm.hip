@@ -17,6 +17,7 @@
 // in-kernel form of the pad -> matmul -> slice steps of the paper's pad_mm
 // case study, appendix Sec. 8.2, without materialising any padding).
 #include <algorithm>
+#include <atomic>
 
 #include "device_common.h"
 
@@ -2332,11 +2333,16 @@ GemmConfig gemm_pick_config_trans(optimus_dtype dt, const optimus_linear_desc* d
 }
 
 int gemm_resident_per_cu(const GemmConfig& cfg, optimus_dtype dt, optimus_act act, bool ln, int tr) {
-  int occ = 0;
+  // a property of the kernel instance, the same on every gfx950: asked once
+  static std::atomic<int> known[16][2][8][2][4][2];
+  std::atomic<int>& slot = known[cfg.variant & 15][dt == OPTIMUS_F32][(int)act & 7][ln][tr & 3][cfg.shrt];
+  int occ = slot.load(std::memory_order_relaxed);
+  if (occ > 0) return occ;
   if (gemm_dispatch(cfg, dt, act, ln, tr, nullptr, nullptr, 0, 0, nullptr, &occ) != hipSuccess || occ < 1) {
     (void)hipGetLastError();
     return cfg.occ;
   }
+  slot.store(occ, std::memory_order_relaxed);
   return occ;
 }
 

@@ -2128,9 +2128,18 @@ extern "C" optimus_status optimus_plan_get_info(optimus_plan p, optimus_plan_inf
 }
 
 // ===================================================================== one-shot entry points
-// The table goes up through a pinned staging buffer (per thread, grow-only)
-// into stream-ordered device memory, the group is launched, and the device
-// memory is released in stream order; the call does not wait for the GPU.
+// Small tables (the usual case) are not uploaded at all: the kernels read them
+// straight from a slot of pinned host memory, a few hundred bytes per workgroup,
+// which costs them a microsecond or two where a stream-ordered allocation, an
+// upload and its completion cost the call tens and made the next call wait for
+// this one. Slots come from a bounded pool per device; a slot is handed out
+// again once the event behind its last launch has passed, whatever the thread
+// or stream. Larger tables, and groups that need device scratch, go up through
+// a pinned staging buffer (per thread, grow-only) into stream-ordered device
+// memory that is released in stream order; so do groups whose kernels read
+// their table over and over (the fused split-op-cat's chunk map) or write into
+// it, and every call under stream capture, whose launch may run again after a
+// slot would have been reused. The calls do not wait for the GPU unless every slot is still in use.
 namespace {
 struct Staging {
   void* host = nullptr;
@@ -2139,10 +2148,84 @@ struct Staging {
   bool pending = false;
 };
 thread_local Staging* tl_stage = nullptr;  // intentionally never freed (process lifetime)
+
+constexpr size_t kSlotBytes = 8192;  // larger tables have so many workgroups that an upload is cheaper
+constexpr int kMaxSlots = 64, kSlotDevices = 64;
+struct Slot {
+  char* host = nullptr;
+  hipEvent_t ev = nullptr;  // behind the last launch that reads the slot
+};
+struct SlotPool {
+  std::mutex mu;
+  std::vector<Slot*> idle;  // oldest use first
+  int made = 0;
+};
+SlotPool* slot_pool(int dev) {
+  static SlotPool* pools = new SlotPool[kSlotDevices];  // never freed (process lifetime)
+  return dev >= 0 && dev < kSlotDevices ? pools + dev : nullptr;
+}
+
+// A slot nobody reads any more, or null (no slot to be had: take the upload path).
+Slot* take_slot(SlotPool* pool) {
+  std::unique_lock<std::mutex> lock(pool->mu);
+  if (!pool->idle.empty()) {
+    Slot* s = pool->idle.front();
+    const bool ready = hipEventQuery(s->ev) == hipSuccess;
+    if (!ready) (void)hipGetLastError();  // "not ready" is no error of the launch that follows
+    if (ready || pool->made >= kMaxSlots) {
+      pool->idle.erase(pool->idle.begin());
+      lock.unlock();
+      if (hipEventSynchronize(s->ev) == hipSuccess) return s;
+      lock.lock();
+      pool->idle.push_back(s);
+      return nullptr;
+    }
+  }
+  if (pool->made >= kMaxSlots) return nullptr;  // every slot is in another thread's hands
+  ++pool->made;
+  lock.unlock();
+  Slot* s = new (std::nothrow) Slot();
+  if (s && hipHostMalloc((void**)&s->host, kSlotBytes, hipHostMallocPortable) == hipSuccess &&
+      hipEventCreateWithFlags(&s->ev, hipEventDisableTiming) == hipSuccess)
+    return s;
+  (void)hipGetLastError();
+  if (s && s->host) (void)hipHostFree(s->host);
+  delete s;
+  lock.lock();
+  --pool->made;
+  return nullptr;
+}
 }  // namespace
+
+static optimus_status run_uploaded(HostPlan& hp, hipStream_t stream);
 
 static optimus_status run_oneshot(HostPlan& hp, hipStream_t stream) {
   if (hp.G == 0) return OPTIMUS_OK;
+  const size_t n = hp.blob.bytes.size();
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  int dev = -1;
+  if (n > kSlotBytes || hp.scratch_bytes || !hp.table_fixups.empty() || hp.q_scaled || hp.soc_fused ||
+      hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+      hipGetDevice(&dev) != hipSuccess)
+    return run_uploaded(hp, stream);
+  SlotPool* pool = slot_pool(dev);
+  Slot* s = pool ? take_slot(pool) : nullptr;
+  if (!s) return run_uploaded(hp, stream);
+  memcpy(s->host, hp.blob.bytes.data(), n);
+  hipError_t e = launch_grouped(hp, s->host, stream);
+  // whatever was launched reads the slot until this event (or, if it cannot be
+  // recorded, until the stream is idle)
+  const hipError_t r = hipEventRecord(s->ev, stream);
+  if (r != hipSuccess) (void)hipStreamSynchronize(stream);
+  {
+    std::lock_guard<std::mutex> lock(pool->mu);
+    pool->idle.push_back(s);
+  }
+  if (e == hipSuccess) e = r;
+  return e == hipSuccess ? OPTIMUS_OK : hip_fail(e, "one-shot: launch");
+}
+
+static optimus_status run_uploaded(HostPlan& hp, hipStream_t stream) {
   if (!tl_stage) tl_stage = new Staging();
   Staging& sg = *tl_stage;
   const size_t n = std::max<size_t>(hp.blob.bytes.size(), 256);
