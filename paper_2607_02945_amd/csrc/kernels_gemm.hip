@@ -626,15 +626,20 @@ __global__ __launch_bounds__(WM* WN * 64) void grouped_gemm_kernel(const DevLine
         __syncthreads();
       }
     } else {
+      // one LDS stage, the next step's loads in flight during the MFMA: half
+      // the LDS of two stages, so five or six workgroups per CU for four (fp32
+      // 64x64, 16 members of 2048 rows, K and N of 64 to 512: 72 us on two
+      // stages, 70 on one; 12 bf16 members of 375 rows on 128x64: 14.0 -> 12.2
+      // us against loads that waited for the step before)
+      gload(kbeg);
+      load_col_params<T, BN, LN>(sBias, sGamma, sBeta, d, n0, Nr);
       for (int kb = 0; kb < nk; ++kb) {
-        gload(kbeg + kb * BK);
-        if (kb == 0) load_col_params<T, BN, LN>(sBias, sGamma, sBeta, d, n0, Nr);
         lstore(0, kbeg + kb * BK);
         __syncthreads();
+        if (kb + 1 < nk) gload(kbeg + (kb + 1) * BK);
         compute(0, wn);
         __syncthreads();
       }
-      if (nk == 0) load_col_params<T, BN, LN>(sBias, sGamma, sBeta, d, n0, Nr);
     }
 
     if constexpr (TX) {
@@ -1970,7 +1975,7 @@ static const GemmVariant kVariants[] = {
     {128, 64, 256, 4, "grouped_gemm_bf16_128x64x64_w4x1_s1"},
     {128, 128, 256, 2, "grouped_gemm_bf16_128x128x64_w2x2_s2"},
     {256, 256, 512, 1, "grouped_gemm_bf16_256x256x64_w2x4_s2"},
-    {64, 64, 256, 4, "grouped_gemm_f32_64x64x32_w2x2_s2"},
+    {64, 64, 256, 4, "grouped_gemm_f32_64x64x32_w2x2_s1"},
     {256, 256, 512, 1, "grouped_gemm_dma_bf16_256x256x64_w2x4"},
     {128, 128, 256, 2, "grouped_gemm_dma_bf16_128x128x64_w2x2"},
     {64, 128, 256, 1, "grouped_gemm_f32_64x128x64_w2x2_s2"},
@@ -2262,7 +2267,7 @@ static hipError_t gemm_dispatch(const GemmConfig& cfg, optimus_dtype dt, optimus
     switch (cfg.variant) {
       case 1: return launch_trans<bf16_t, 128, 128, 64, 2, 2, 2>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
       case 2: return launch_trans<bf16_t, 256, 256, 64, 2, 4, 2>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
-      case 3: return launch_trans<float, 64, 64, 32, 2, 2, 2>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
+      case 3: return launch_trans<float, 64, 64, 32, 2, 2, 1>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
       case 4: return launch_dma_trans<256, 256, 2, 4>(tr, act, descs, tiles, n, grid, stream, occ);
       case 5: return launch_dma_trans<128, 128, 2, 2>(tr, act, descs, tiles, n, grid, stream, occ);
       case 6: return launch_trans<float, 64, 128, 64, 2, 2, 2>(tr, cfg.shrt, descs, tiles, n, grid, stream, occ);
@@ -2273,7 +2278,7 @@ static hipError_t gemm_dispatch(const GemmConfig& cfg, optimus_dtype dt, optimus
     case 0: return launch_shape<bf16_t, 128, 64, 64, 4, 1, 1>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
     case 1: return launch_shape<bf16_t, 128, 128, 64, 2, 2, 2>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
     case 2: return launch_shape<bf16_t, 256, 256, 64, 2, 4, 2>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
-    case 3: return launch_shape<float, 64, 64, 32, 2, 2, 2>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
+    case 3: return launch_shape<float, 64, 64, 32, 2, 2, 1>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
     case 4: return launch_dma<256, 256, 2, 4>(act, ln, descs, tiles, n, grid, stream, occ);
     case 5: return launch_dma<128, 128, 2, 2>(act, ln, descs, tiles, n, grid, stream, occ);
     case 6: return launch_shape<float, 64, 128, 64, 2, 2, 2>(act, ln, cfg.shrt, descs, tiles, n, grid, stream, occ);
