@@ -18,7 +18,9 @@
 #include <mutex>
 #include <new>
 #include <cstddef>
+#include <numeric>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "optimus.h"
@@ -667,37 +669,45 @@ static void build_rows(HostPlan& hp, const std::vector<DevRows>& members, bool l
 // contiguous slices of it to each L2); the per-member CHAIN launches then
 // read a member-major copy of the list.
 static void build_gemm_set(HostPlan& hp, GemmSet& gs, const GemmConfig& cfg, int tr, const std::vector<DevLinear>& descs,
-                           const std::vector<int>& ids, int group_size, optimus_act act, bool ln, int splits = 1) {
+                           const std::vector<int>& ids, int group_size, optimus_act act, bool ln) {
   const int n = (int)descs.size();
   gs.cfg = cfg;
   gs.tr = tr;
   gs.act = act;
   std::vector<int> order(n);
   for (int i = 0; i < n; ++i) order[i] = i;
+  // the reduction one work item does: all of K, or one split of it
+  auto red_len = [](const DevLinear& o) { return o.ws || o.kchunk ? std::min(o.K, o.kchunk) : o.K; };
   // the streaming kernel's item cost is its rows' bytes, x row plus y row
   // (K + N values); the tiled kernels' tile cost grows with K
   if (cfg.variant == 9)
     std::stable_sort(order.begin(), order.end(),
                      [&](int a, int b) { return descs[a].K + descs[a].N > descs[b].K + descs[b].N; });
   else
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return descs[a].K > descs[b].K; });
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return red_len(descs[a]) > red_len(descs[b]); });
   const int bm = cfg.bm, bn = cfg.bn;
   auto member_tiles = [&](std::vector<GemmTile>& tl, int i, int64_t mb) {
     const int64_t nbs = (descs[i].N + bn - 1) / bn;
     // split index fastest: measured on the weight gradient, this beats the
     // split-major order (all tiles of one reduction range side by side on
     // one L2) by 3.5 % despite 16 % more HBM reads
+    const int sp = descs[i].splits > 1 ? descs[i].splits : 1;
     for (int64_t nb = 0; nb < nbs; ++nb)
-      for (int ks = 0; ks < splits; ++ks) tl.push_back(GemmTile{i, (int32_t)mb, (int32_t)nb, ks});
+      for (int ks = 0; ks < sp; ++ks) tl.push_back(GemmTile{i, (int32_t)mb, (int32_t)nb, ks});
   };
   // member-major list (and the CHAIN ranges)
   std::vector<GemmTile> chain_tiles;
   gs.chain.assign(group_size, RowLaunch{});
-  for (int i : order) {
+  bool parts = false;  // some member has two table entries (its unsplit and its split rows, one after the other)
+  for (int i = 1; i < n; ++i) parts = parts || ids[i] == ids[i - 1];
+  std::vector<int> chain_order = order;
+  if (parts) std::iota(chain_order.begin(), chain_order.end(), 0);
+  for (int i : chain_order) {
     const int first = (int)chain_tiles.size();
     for (int64_t mb = 0; mb < (descs[i].M + bm - 1) / bm; ++mb) member_tiles(chain_tiles, i, mb);
-    gs.chain[ids[i]].first_tile = first;
-    gs.chain[ids[i]].num_tiles = (int)chain_tiles.size() - first;
+    RowLaunch& c = gs.chain[ids[i]];
+    if (c.num_tiles == 0) c.first_tile = first;
+    c.num_tiles += (int)chain_tiles.size() - first;
   }
   // grouped list: a run of consecutive members (in `order`) that share x is
   // walked in groups of kSharedMBlocks M-blocks: for each group, every
@@ -750,7 +760,7 @@ static void build_gemm_set(HostPlan& hp, GemmSet& gs, const GemmConfig& cfg, int
   // last round's items spread over all XCDs; empty positions are padding.
   // Only for members of one K: with K unequal the heavy-first list relies on
   // every round mixing all XCDs (dealt, one XCD would take all the long items).
-  bool reordered = false;  // the grouped list is no longer member-major
+  bool reordered = parts;  // the grouped list is no longer member-major
   {
     const int64_t T = (int64_t)tiles.size();
     int64_t g = std::min<int64_t>((T + 7) / 8 * 8, cap);
@@ -1075,39 +1085,67 @@ static optimus_status build_linear_backward(const optimus_linear_grad_desc* d, i
     // on MI355X: a direct-to-LDS K step at 4.6 TFLOP/s per CU (256x256) and
     // 3.6 (128x128), HBM at 4.7 TB/s shared by the slots. A larger split count
     // must gain 3 %: the estimate is that close to the measured times.
-    double out_elems = 0.0;
-    for (const auto& o : dws) out_elems += (double)o.M * o.N;
-    auto est_of = [&](const GemmConfig& c, int sp) {
+    // split rows of one table entry under a tail split: the last `panels` of
+    // its M-blocks, counted from the last member back until `tail` tiles are split
+    auto split_panels = [&](const GemmConfig& c, int64_t tail) {
+      std::vector<int64_t> panels(dws.size(), 0);
+      for (size_t i = dws.size(); i-- > 0 && tail > 0;) {
+        const int64_t nbs = (dws[i].N + c.bn - 1) / c.bn, mbs = (dws[i].M + c.bm - 1) / c.bm;
+        panels[i] = std::min(mbs, (tail + nbs - 1) / nbs);
+        tail -= panels[i] * nbs;
+      }
+      return panels;
+    };
+    auto tile_count = [&](const GemmConfig& c) {
+      int64_t n = 0;
+      for (const auto& o : dws) n += (int64_t)((o.M + c.bm - 1) / c.bm) * ((o.N + c.bn - 1) / c.bn);
+      return n;
+    };
+    auto slots_of = [&](const GemmConfig& c) {
+      return (int64_t)device_cu_count() * gemm_resident_per_cu(c, dt, OPTIMUS_ACT_NONE, false, 3);
+    };
+    // tail < 0: every tile split sp ways; else only the last `tail` tiles
+    auto est_of = [&](const GemmConfig& c, int sp, int64_t tail = -1) {
       const int bkc = c.variant == 3 ? 32 : 64;
       const int occ = gemm_resident_per_cu(c, dt, OPTIMUS_ACT_NONE, false, 3);
       const int64_t slots = (int64_t)device_cu_count() * occ;
       const double cu_rate = c.variant == 4 ? 4.6e12 : c.variant == 5 ? 3.6e12
                            : (c.variant == 3 || c.variant == 6) ? 0.4e12 : 3.0e12;
       const double t_step = 2.0 * c.bm * c.bn * bkc / (cu_rate / occ);
-      const double t_out = (double)c.bm * c.bn * (sp > 1 ? 4.0 : (double)s) / (4.7e12 / (double)slots);
-      std::vector<int64_t> steps;  // per work item, in list order
-      for (const auto& o : dws) {
+      const double t_byte = (double)c.bm * c.bn / (4.7e12 / (double)slots);
+      const std::vector<int64_t> panels = tail < 0 ? std::vector<int64_t>() : split_panels(c, tail);
+      std::vector<std::pair<int64_t, double>> items, last;  // K steps and output time, unsplit tiles first
+      double split_elems = 0.0;
+      for (size_t i = 0; i < dws.size(); ++i) {
+        const DevLinear& o = dws[i];
+        const int64_t nbs = (o.N + c.bn - 1) / c.bn, mbs = (o.M + c.bm - 1) / c.bm;
+        const int64_t sm = tail < 0 ? (sp > 1 ? mbs : 0) : panels[i];
+        for (int64_t t = 0; t < (mbs - sm) * nbs; ++t) items.push_back({(o.K + bkc - 1) / bkc, t_byte * (double)s});
+        if (!sm) continue;
         const int64_t kc = ((o.K + sp - 1) / sp + bkc - 1) / bkc * bkc;
         if ((int64_t)(sp - 1) * kc >= o.K) return -1.0;  // an empty split
-        const int64_t tiles = ((o.M + c.bm - 1) / c.bm) * ((o.N + c.bn - 1) / c.bn);
-        for (int64_t t = 0; t < tiles; ++t)
-          for (int k = 0; k < sp; ++k) steps.push_back((std::min<int64_t>(o.K, (k + 1) * kc) - k * kc + bkc - 1) / bkc);
+        split_elems += (double)(o.M - (mbs - sm) * c.bm) * o.N;
+        for (int64_t t = 0; t < sm * nbs; ++t)
+          for (int k = 0; k < sp; ++k)
+            last.push_back({(std::min<int64_t>(o.K, (k + 1) * kc) - k * kc + bkc - 1) / bkc, t_byte * 4.0});
       }
-      const int64_t n8 = ((int64_t)steps.size() + 7) / 8 * 8;
+      items.insert(items.end(), last.begin(), last.end());
+      const int64_t n8 = ((int64_t)items.size() + 7) / 8 * 8;
       int64_t grid = std::min<int64_t>(n8, slots);
       if (grid >= 8) grid -= grid % 8;
       grid = std::max<int64_t>(grid, 1);
       std::vector<double> load((size_t)grid, 0.0);
-      for (size_t i = 0; i < steps.size(); ++i) load[i % grid] += (double)steps[i] * t_step + t_out;
+      for (size_t i = 0; i < items.size(); ++i) load[i % grid] += (double)items[i].first * t_step + items[i].second;
       const double makespan = *std::max_element(load.begin(), load.end());
       // the reduce reads every split's partials and writes the output once
       // (plus about 6 us of launch gap and ramp)
-      return makespan + (sp > 1 ? out_elems * (4.0 * sp + (double)s) / 4.7e12 + 6e-6 : 0.0);
+      return makespan + (split_elems > 0.0 ? split_elems * (4.0 * sp + (double)s) / 4.7e12 + 6e-6 : 0.0);
     };
     const int n_dw = (int32_t)dw_shape.size();
     GemmConfig cfg = gemm_pick_config_trans(dt, dw_shape.data(), n_dw, true, 0, po.pin);
     if (cfg.variant < 0) return tile_unsupported(po, "plan_linear_backward (dW)");
     int splits = 1;
+    int64_t tail = -1;  // >= 0: only the last `tail` tiles are split
     {
       std::vector<GemmConfig> cands{cfg};
       if (dt == OPTIMUS_BF16 && po.pin < 0)
@@ -1118,6 +1156,7 @@ static optimus_status build_linear_backward(const optimus_linear_grad_desc* d, i
       double best = -1.0;
       for (const GemmConfig& c : cands) {
         int sp_best = 1;
+        int64_t tail_best = -1;
         double e_best = est_of(c, 1);
         for (int sp = 2; sp <= 16; ++sp) {
           const double e = est_of(c, sp);
@@ -1126,10 +1165,27 @@ static optimus_status build_linear_backward(const optimus_linear_grad_desc* d, i
             sp_best = sp;
           }
         }
+        // Whole rounds of unsplit tiles and only the tiles of the last,
+        // partial round split: the same even finish, a fraction of the fp32
+        // partials (the persistent kernels, whose item i runs on slot i mod
+        // grid). 32 members, K = 1024, N of 256 to 1024, batch 16384: 3 ways
+        // everywhere 1888 us for the whole backward, the last 64 of 320 tiles 4
+        // ways 1802 us.
+        const int64_t T = tile_count(c), slots = slots_of(c), rest = T % slots;
+        if (T > slots && rest > 0 && (c.variant == 1 || c.variant == 2 || c.variant == 4 || c.variant == 5))
+          for (int sp = 2; sp <= 16; ++sp) {
+            const double e = est_of(c, sp, rest);
+            if (e >= 0.0 && e < e_best * 0.97) {
+              e_best = e;
+              sp_best = sp;
+              tail_best = rest;
+            }
+          }
         if (best < 0.0 || e_best < best * 0.99) {
           best = e_best;
           cfg = c;
           splits = sp_best;
+          tail = tail_best;
         }
       }
     }
@@ -1139,14 +1195,45 @@ static optimus_status build_linear_backward(const optimus_linear_grad_desc* d, i
       if (est_of(cfg, po.splits) < 0.0)
         return fail(OPTIMUS_ERR_UNSUPPORTED, "plan_linear_backward: wgrad_splits %d leaves a split empty", po.splits);
       splits = po.splits;
+      tail = -1;
+    }
+    if (splits > 1 && tail >= 0) {
+      // a member's split rows (its last M-blocks) become a table entry of their
+      // own behind its unsplit rows
+      const std::vector<int64_t> panels = split_panels(cfg, tail);
+      std::vector<DevLinear> all;
+      std::vector<int> all_ids;
+      for (size_t i = 0; i < dws.size(); ++i) {
+        DevLinear o = dws[i];
+        const int64_t row = ((o.M + cfg.bm - 1) / cfg.bm - panels[i]) * cfg.bm;  // the first split row
+        if (row > 0) {
+          o.M = (int32_t)std::min<int64_t>(o.M, row);
+          all.push_back(o);
+          all_ids.push_back(dw_ids[i]);
+        }
+        if (panels[i] > 0) {
+          o = dws[i];
+          o.x = (const char*)o.x + row * (int64_t)s;
+          o.y = (char*)o.y + row * o.ldy * (int64_t)s;
+          if (o.xsum) o.xsum = (char*)o.xsum + row * (int64_t)s;
+          o.M -= (int32_t)row;
+          o.splits = splits;
+          all.push_back(o);
+          all_ids.push_back(dw_ids[i]);
+        }
+      }
+      dws.swap(all);
+      dw_ids.swap(all_ids);
+    } else if (splits > 1) {
+      for (DevLinear& o : dws) o.splits = splits;
     }
     if (splits > 1) {
       std::vector<SplitReduceItem> red;
       for (size_t i = 0; i < dws.size(); ++i) {
         DevLinear& o = dws[i];
+        if (o.splits <= 1) continue;
         const int64_t kc = ((o.K + splits - 1) / splits + bk - 1) / bk * bk;
         o.kchunk = (int32_t)kc;
-        o.splits = splits;
         const int64_t floats = (int64_t)splits * o.M * o.N + (int64_t)splits * o.M;
         const size_t off = (hp.scratch_bytes + 255) & ~(size_t)255;
         o.ws = (float*)(uintptr_t)off;
@@ -1169,11 +1256,11 @@ static optimus_status build_linear_backward(const optimus_linear_grad_desc* d, i
         c.grid = std::max(1, std::min(c.num_tiles, cap));
       }
     }
-    build_gemm_set(hp, gs, cfg, 3, dws, dw_ids, G, OPTIMUS_ACT_NONE, false, splits);
-    for (size_t i = 0; i < dws.size() && splits > 1; ++i)
-      hp.scratch_fixups.push_back(gs.descs_off + i * sizeof(DevLinear) + offsetof(DevLinear, ws));
+    build_gemm_set(hp, gs, cfg, 3, dws, dw_ids, G, OPTIMUS_ACT_NONE, false);
+    for (size_t i = 0; i < dws.size(); ++i)
+      if (dws[i].splits > 1) hp.scratch_fixups.push_back(gs.descs_off + i * sizeof(DevLinear) + offsetof(DevLinear, ws));
     name += std::string(name.empty() ? "" : "+") + gs.cfg.name + "_wgrad" +
-            (splits > 1 ? "_split" + std::to_string(splits) : "");
+            (splits > 1 ? "_split" + std::to_string(splits) + (tail >= 0 ? "_tail" : "") : "");
   }
   for (int i = 0; i < hp.n_gs; ++i) {
     hp.work_items += hp.gs[i].real_tiles;

@@ -145,3 +145,29 @@ def test_linear_backward(dtype, tile, splits):
         for what, got, ref in (("dx", dxs[i].view, rdx), ("dw", dws[i].view, rdw), ("db", dbs[i], rdb)):
             assert_close(host64(got), ref, dtype, f"tile {tile} {LINEAR[i]} {what}")
         assert dxs[i].surroundings_kept() and dws[i].surroundings_kept(), f"{LINEAR[i]}: wrote beside its rows"
+
+
+@pytest.mark.parametrize("cols", [1024, 1000])  # whole tiles; a partial last M-block (and column block)
+def test_weight_gradient_tail_split(cols):
+    """More 256 x 256 tiles of dW than CUs, not a multiple: the plan splits the
+    batch of the last round's tiles only. Every tile and db, grouped and chain,
+    against fp64 products."""
+    say(f"[wgrad tail split] cols={cols}")
+    g = torch.Generator(device="cuda").manual_seed(10)
+    G, M = 21, 4096
+    mk = lambda r, c: torch.randn(r, c, device="cuda", generator=g).bfloat16()
+    xs, dys = [mk(M, 1024) for _ in range(G)], [mk(M, cols) for _ in range(G)]
+    out = {}
+    for mode in ("grouped", "chain"):
+        dws = [torch.full((cols, 1024), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(G)]
+        dbs = [torch.full((cols,), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(G)]
+        p = B.optimus_plan_linear_backward(xs, xs, dys, None, dws, dbs)
+        assert "_tail" in p.info()["kernel"], p.info()["kernel"]
+        for _ in range(2):
+            p.execute(mode)
+        out[mode] = (dws, dbs)
+    for i in range(G):
+        ref, rb = dys[i].double().T.contiguous() @ xs[i].double(), dys[i].double().sum(0)
+        assert_close(host64(out["grouped"][0][i]), ref.cpu().numpy(), "bf16", f"member {i} dw")
+        assert_close(host64(out["grouped"][1][i]), rb.cpu().numpy(), "bf16", f"member {i} db")
+        assert torch.equal(out["grouped"][0][i], out["chain"][0][i]) and torch.equal(out["grouped"][1][i], out["chain"][1][i])
