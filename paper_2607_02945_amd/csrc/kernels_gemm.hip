@@ -18,6 +18,8 @@
 // case study, appendix Sec. 8.2, without materialising any padding).
 #include <algorithm>
 #include <atomic>
+#include <utility>
+#include <vector>
 
 #include "device_common.h"
 
@@ -2036,6 +2038,39 @@ bool gemm_dma_wt_ok(const optimus_linear_desc* d, int32_t G) {
 
 int gemm_ln_max_n(optimus_dtype dt) { return dt == OPTIMUS_F32 ? 128 : 256; }
 
+// Whether the direct-to-LDS 128x128 tiles are the faster cover of a group that
+// fills the CUs with 256x256 ones: where they pad much less, i.e. widths just
+// past a multiple of 256. A tile's time is its K steps plus about 4 for the
+// epilogue. The 256x256 tiles run one per CU in the static schedule's rounds;
+// the 128x128 ones two per CU at 5/8 of a large tile's time each (0.5 by area,
+// the rest lost to their lower reuse), and the second workgroup softens the
+// last round to half a tile. Measured (26 members of 4096 rows, K = 512, us on
+// 256 / 128): N = 64 31 / 23, 128 32 / 28, 192 36 / 38, 256 38 / 41, 320 64 / 54,
+// 384 66 / 55, 448 69 / 69, 512 74 / 73; 1024 rows: N = 320 18 / 19; 16 members of
+// 16384 rows, K = 1024: N = 128 150 / 117, 256 161 / 200, 384 266 / 273, 512 284 / 374.
+// The input gradient, whose widths are the layers' inputs, behaves alike
+// (towers of 64 to 512 inputs and 512 outputs, batch 4096: 58 / 46).
+static bool gemm_tiles_128_ahead(const optimus_linear_desc* d, int32_t G) {
+  const int cus = device_cu_count();
+  std::vector<std::pair<int64_t, int64_t>> big;  // (time of a tile, tiles) per member
+  double sum128 = 0.0;
+  int64_t longest = 0;
+  for (int g = 0; g < G; ++g) {
+    const int64_t c = (d[g].K + 63) / 64 + 4;
+    big.push_back({c, ((d[g].M + 255) / 256) * ((d[g].N + 255) / 256)});
+    sum128 += (double)c * (double)(((d[g].M + 127) / 128) * ((d[g].N + 127) / 128));
+    longest = std::max(longest, c);
+  }
+  std::sort(big.begin(), big.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  // the first workgroup's share of the list, longest tiles first: items 0, cus, 2 cus, ...
+  int64_t t256 = 0, at = 0, next = 0;
+  for (const auto& m : big) {
+    at += m.second;
+    for (; next < at; next += cus) t256 += m.first;
+  }
+  return (sum128 / (2.0 * cus) + 0.5 * (double)longest) * 0.625 < 0.97 * (double)t256;
+}
+
 GemmConfig gemm_pick_config(optimus_dtype dt, const optimus_linear_desc* d, int32_t G, bool ln, int pin) {
   int64_t maxN = 0, maxK = 0, minK = INT32_MAX;
   double tiles256 = 0.0;
@@ -2096,8 +2131,9 @@ GemmConfig gemm_pick_config(optimus_dtype dt, const optimus_linear_desc* d, int3
     v = tiles256 >= 3.0 * cus && area > 192.0 * rows ? 2 : area > 384.0 * rows && tiles128 >= cus ? 1 : 0;
   } else if (tiles256 >= 0.5 * device_cu_count() || (ln && maxN > 128)) {
     // measured over groups of 64 to 4096 256x256 tiles: the 256x256 tile wins
-    // from half a tile per CU on (and is the one that holds rows past 128)
-    v = dma ? 4 : 2;
+    // from half a tile per CU on (and is the one that holds rows past 128),
+    // unless 128x128 tiles pad the members' widths much less
+    v = dma ? (!(ln && maxN > 128) && gemm_tiles_128_ahead(d, G) ? 5 : 4) : 2;
   } else {
     // smaller groups need the 128x128 tile to spread over the CUs
     v = dma ? 5 : 1;
