@@ -74,11 +74,7 @@ __global__ __launch_bounds__(kRowThreads) void grouped_act_backward_kernel(const
 // by the caller) and read where they are used. ACT != 0: the backward of the
 // fused LayerNorm + activation -- the incoming gradient is the activation
 // output's, and is multiplied by act'(gamma * xhat + beta), recomputed here
-// once per value: the pass that forms the row sums leaves the products in
-// the wave's slot sPart (free until the tile's sums are written there) and
-// the output pass reads them back (the derivative is two transcendentals per
-// value; large_group's LayerNorm + tanh backward 454 -> 413 us). Keeping
-// xhat there too saved nothing.
+// once per value (the derivative is two transcendentals).
 // RAG: rows of any width from VEC values on, at any alignment, as the forward
 // takes them: the chunk with a row's last values is the 16 bytes that end at
 // the row's end, its first `dup` values left out of every sum (gamma and beta
@@ -143,64 +139,56 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
   fetch(rt.row0 + wave * rpw + sub);
   // every lane of the wave runs the loop the same number of times (the
   // lane-group sums need all 64); rows past the tile contribute nothing.
-  // The current row stays packed (cx, cg) and is unpacked in each pass, so
-  // that it and the prefetched next row fit in registers together.
+  // Each value is unpacked, centred and multiplied by act' once and stays in
+  // registers; a chunk's sums are masked once per chunk, not per value. The
+  // vector instructions, some 40 per value before, weigh about as much as the
+  // row's memory time here.
   for (int base = rt.row0; base < end; base += rpb) {
     const int r = base + wave * rpw + sub;
     const bool valid = r < end;
-    u32x4 cx[MAXC], cg[MAXC];
+    float x[MAXC][VEC], g[MAXC][VEC];  // x: the row, then centred, then xhat
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
-      cx[j] = rx[j];
-      cg[j] = rg[j];
+      Elem<T>::unpack(rx[j], x[j]);  // zero where out of range
+      Elem<T>::unpack(rg[j], g[j]);
     }
     if (base + rpb < end) fetch(r + rpb);
     float s = 0.f;
 #pragma unroll
-    for (int j = 0; j < MAXC; ++j) {
-      float x[VEC];
-      Elem<T>::unpack(cx[j], x);
+    for (int j = 0; j < MAXC; ++j)
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) s += !RAG || e >= dup[j] ? x[e] : 0.f;
-    }
+      for (int e = 0; e < VEC; ++e) s += !RAG || e >= dup[j] ? x[j][e] : 0.f;
     const float mean = group_sum(s, L) * d.inv_cols;
     float q = 0.f;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
-      const bool in = valid && (j * L + li) < cpr;
-      float x[VEC];
-      Elem<T>::unpack(cx[j], x);
+      float qj = 0.f;
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
-        const float t = x[e] - mean;
-        q += in && (!RAG || e >= dup[j]) ? t * t : 0.f;
+        x[j][e] -= mean;
+        qj += !RAG || e >= dup[j] ? x[j][e] * x[j][e] : 0.f;
       }
+      q += valid && (j * L + li) < cpr ? qj : 0.f;
     }
     const float rstd = __builtin_amdgcn_rsqf(group_sum(q, L) * d.inv_cols + d.eps);
-    // this lane's products g * act' of chunk j, element group h (ACT != 0)
-    auto gslot = [&](int j, int h) { return (f32x4*)sPart + (j * (VEC / 4) + h) * 64 + lane; };
     float sg = 0.f, sgx = 0.f;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
       const bool in = valid && (j * L + li) < cpr;
-      float x[VEC], g[VEC], gm[VEC], xh[VEC];
-      Elem<T>::unpack(cx[j], x);
-      Elem<T>::unpack(cg[j], g);
+      float gm[VEC], sgj = 0.f, sgxj = 0.f;
       gamma_of(j, gm);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) xh[e] = (x[e] - mean) * rstd;
-      grad_in(j, gm, xh, g);
-      if constexpr (ACT != 0) {
-#pragma unroll
-        for (int h = 0; h < VEC / 4; ++h) *gslot(j, h) = f32x4{g[4 * h], g[4 * h + 1], g[4 * h + 2], g[4 * h + 3]};
-      }
+      for (int e = 0; e < VEC; ++e) x[j][e] *= rstd;
+      grad_in(j, gm, x[j], g[j]);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
-        const float gg = g[e] * gm[e];
-        const bool ine = in && (!RAG || e >= dup[j]);
-        sg += ine ? gg : 0.f;
-        sgx += ine ? gg * xh[e] : 0.f;
+        const float gg = g[j][e] * gm[e];
+        const bool ine = !RAG || e >= dup[j];
+        sgj += ine ? gg : 0.f;
+        sgxj += ine ? gg * x[j][e] : 0.f;
       }
+      sg += in ? sgj : 0.f;
+      sgx += in ? sgxj : 0.f;
     }
     const float mg = group_sum(sg, L) * d.inv_cols;
     const float mgx = group_sum(sgx, L) * d.inv_cols;
@@ -209,28 +197,13 @@ __device__ __forceinline__ void lnb_rows_vec(const DevRowsGrad& d, const RowTile
     for (int j = 0; j < MAXC; ++j) {
       const int c = j * L + li;
       if (valid && c < cpr) {
-        float x[VEC], g[VEC], gm[VEC], o[VEC], xh[VEC];
-        Elem<T>::unpack(cx[j], x);
+        float gm[VEC], o[VEC];
         gamma_of(j, gm);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) xh[e] = (x[e] - mean) * rstd;
-        if constexpr (ACT != 0) {
-#pragma unroll
-          for (int h = 0; h < VEC / 4; ++h) {
-            const f32x4 v = *gslot(j, h);
-            g[4 * h] = v.x;
-            g[4 * h + 1] = v.y;
-            g[4 * h + 2] = v.z;
-            g[4 * h + 3] = v.w;
-          }
-        } else {
-          Elem<T>::unpack(cg[j], g);
-        }
-#pragma unroll
         for (int e = 0; e < VEC; ++e) {
-          o[e] = rstd * (g[e] * gm[e] - mg - xh[e] * mgx);
-          accG[j][e] += g[e] * xh[e];
-          accB[j][e] += g[e];
+          o[e] = rstd * (g[j][e] * gm[e] - mg - x[j][e] * mgx);
+          accG[j][e] += g[j][e] * x[j][e];
+          accB[j][e] += g[j][e];
         }
         st16u_nt(orow + first_of(c), Elem<T>::pack(o));
       }
