@@ -1616,7 +1616,7 @@ __global__ __launch_bounds__(256, 4) void grouped_gemm_stream_kernel(const DevLi
 // kernel with no MFMA: each lane owns whole rows, multiplies a row's K values
 // by the member's weights (fp32 FMAs, ascending k) and writes the row's N
 // outputs. A work item is kSkinnyRows rows of one member, walked in passes
-// of RPL rows per lane (8 for the small classes, 4 for 8 x 8), and a lane
+// of RPL rows per lane (8 for the small classes, 4 for the others), and a lane
 // loads all of a pass's rows before it uses any. A member's weights and bias are staged in LDS as fp32 when a
 // workgroup's items reach it (while its first rows are in flight) and read
 // back as broadcasts. A uniform branch per item picks the smallest shape class
@@ -1758,6 +1758,160 @@ __device__ __forceinline__ void skinny_item(const DevLinear& d, int r0, int coun
   }
 }
 
+// Members whose x and y rows are contiguous: a wave's rows of a pass are one
+// run of values, moved in consecutive 16-byte chunks whatever K and N are (rows
+// of other lengths took several strided or 4-byte accesses each). Lane l takes
+// chunks l + 64 j; where a row is not one chunk the values change places
+// through the wave's own 8 KB of LDS, chunk by chunk in and row by row out for
+// x, and back for y, with no block barrier. The last item's run may end
+// inside a chunk, which is then moved value by value. Bound by HBM; two members
+// of 8e6 rows, K x N, us before and after: fp32 4 x 8 178 -> 141 (5.4 TB/s),
+// 8 x 4 176 -> 131, 6 x 6 255 -> 139, 5 x 7 302 -> 141; bf16 8 x 8 103 -> 86,
+// 5 x 3 141 -> 74, 4 x 2 99 -> 41.
+constexpr int kSkinnyFlat = 8192;  // LDS bytes per wave
+
+template <typename T, int KV, int NV, int ACT>
+__device__ __forceinline__ void skinny_item_flat(const DevLinear& d, int r0, int count, bool restage, float* sW,
+                                                 float* sB, char* sArea) {
+  constexpr int VEC = Elem<T>::VEC;
+  constexpr int RPL = KV == 4 && NV <= 4 ? 8 : 4;               // rows per lane
+  constexpr int CIN = RPL * KV / VEC, COUT = RPL * NV / VEC;  // most chunks per lane
+  constexpr int ROWS = 64 * RPL, PASS = 4 * ROWS;
+  static_assert(kSkinnyRows % PASS == 0, "whole passes per item");
+  static_assert(ROWS * KV * sizeof(T) <= kSkinnyFlat && ROWS * NV * sizeof(T) <= kSkinnyFlat, "a pass fits the area");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  T* area = (T*)(sArea + wave * kSkinnyFlat);
+#pragma unroll 1
+  for (int p = 0; p < kSkinnyRows && p < count; p += PASS) {
+    const int first = p + wave * ROWS;                             // this wave's first row in the item
+    const int rows = max(0, min(ROWS, count - first));
+    const int nx = rows * d.K, ny = rows * d.N;                    // values of its runs
+    const T* xb = (const T*)d.x + (int64_t)(r0 + first) * d.K;
+    T* yb = (T*)d.y + (int64_t)(r0 + first) * d.N;
+    u32x4 xc[CIN];
+#pragma unroll
+    for (int j = 0; j < CIN; ++j) {
+      const int v = (lane + 64 * j) * VEC;
+      if (v + VEC <= nx) {
+        xc[j] = ld16u_nt(xb + v);
+      } else {
+        float f[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) f[e] = v + e < nx ? Elem<T>::load1(xb, v + e) : 0.f;
+        xc[j] = Elem<T>::pack(f);
+      }
+    }
+    if (p == 0 && restage) {
+      __syncthreads();  // every wave is done with the previous member's weights
+      if (tid < kSkinnyMax * kSkinnyMax) {
+        const int n = tid / kSkinnyMax, k = tid % kSkinnyMax;
+        sW[tid] = (n < d.N && k < d.K) ? Elem<T>::load1(d.w, (int64_t)n * d.ldw + k) : 0.f;
+      }
+      if (tid < kSkinnyMax) sB[tid] = (d.bias && tid < d.N) ? Elem<T>::load1(d.bias, tid) : 0.f;
+      __syncthreads();
+    }
+    float x[RPL][KV];  // rows lane + 64 i
+    if (KV == VEC && d.K == VEC) {
+#pragma unroll
+      for (int i = 0; i < RPL; ++i)
+        if constexpr (KV == VEC) Elem<T>::unpack(xc[i], x[i]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < CIN; ++j)
+        if (64 * j < ROWS * d.K / VEC) *(u32x4*)(area + (lane + 64 * j) * VEC) = xc[j];
+      lds_wave_sync();
+      if (sizeof(T) == 4 && KV == 8 && d.K == 8) {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i)
+#pragma unroll
+          for (int c = 0; c < KV / 4; ++c) {
+            const f32x4 q = *(const f32x4*)((const float*)area + (lane + 64 * i) * 8 + 4 * c);
+            x[i][4 * c] = q.x;
+            x[i][4 * c + 1] = q.y;
+            x[i][4 * c + 2] = q.z;
+            x[i][4 * c + 3] = q.w;
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i)
+#pragma unroll
+          for (int k = 0; k < KV; ++k) {
+            float f = 0.f;
+            if (k < d.K) {
+              const T* q = area + (lane + 64 * i) * d.K + k;
+              if constexpr (sizeof(T) == 4)
+                f = *(const float*)q;
+              else
+                f = bf16_to_f32(*(const uint16_t*)q);
+            }
+            x[i][k] = f;
+          }
+      }
+      lds_wave_sync();  // the area is written again below
+    }
+    float o[RPL][NV];
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+      float w[KV];
+#pragma unroll
+      for (int k = 0; k < KV; ++k) w[k] = sW[n * kSkinnyMax + k];
+      const float b = sB[n];
+#pragma unroll
+      for (int i = 0; i < RPL; ++i) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < KV; ++k) s = fmaf(x[i][k], w[k], s);
+        o[i][n] = act_apply<ACT>(s + b);
+      }
+    }
+    u32x4 yc[COUT];
+    if (NV == VEC && d.N == VEC) {
+#pragma unroll
+      for (int i = 0; i < RPL; ++i)
+        if constexpr (NV == VEC) yc[i] = Elem<T>::pack(o[i]);
+    } else {
+      if (sizeof(T) == 4 && NV == 8 && d.N == 8) {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i)
+#pragma unroll
+          for (int c = 0; c < NV / 4; ++c)
+            *(f32x4*)((float*)area + (lane + 64 * i) * 8 + 4 * c) =
+                f32x4{o[i][4 * c], o[i][4 * c + 1], o[i][4 * c + 2], o[i][4 * c + 3]};
+      } else {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i)
+#pragma unroll
+          for (int n = 0; n < NV; ++n)
+            if (n < d.N) {
+              T* q = area + (lane + 64 * i) * d.N + n;
+              if constexpr (sizeof(T) == 4)
+                *(float*)q = o[i][n];
+              else
+                *(uint16_t*)q = f32_to_bf16(o[i][n]);
+            }
+      }
+      lds_wave_sync();
+#pragma unroll
+      for (int j = 0; j < COUT; ++j)
+        if (64 * j < ROWS * d.N / VEC) yc[j] = *(const u32x4*)(area + (lane + 64 * j) * VEC);
+      lds_wave_sync();  // and by the next pass
+    }
+#pragma unroll
+    for (int j = 0; j < COUT; ++j) {
+      const int v = (lane + 64 * j) * VEC;
+      if (v + VEC <= ny) {
+        st16u_nt(yb + v, yc[j]);
+      } else if (v < ny) {
+        float f[VEC];
+        Elem<T>::unpack(yc[j], f);  // exact both ways: the values are already rounded to T
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+          if (v + e < ny) Elem<T>::store1(yb, v + e, f[e]);
+      }
+    }
+  }
+}
+
 // fp32 members with K = N = 8 and contiguous rows (32 bytes each): a lane pair
 // per row, so that every load and store instruction moves consecutive 16-byte
 // chunks. Thread t takes chunks t + 256 j of the item (chunk c is half c % 2
@@ -1834,11 +1988,12 @@ __device__ __forceinline__ void skinny_item_pairs(const DevLinear& d, int r0, in
 }
 
 template <typename T, int ACT>
-__global__ __launch_bounds__(256) void grouped_gemm_skinny_kernel(const DevLinear* __restrict__ descs,
+__global__ __launch_bounds__(256, 3) void grouped_gemm_skinny_kernel(const DevLinear* __restrict__ descs,
                                                                   const GemmTile* __restrict__ tiles,
                                                                   int32_t num_tiles) {
   __shared__ __align__(16) float sW[kSkinnyMax * kSkinnyMax];
   __shared__ __align__(16) float sB[kSkinnyMax];
+  __shared__ __align__(16) char sArea[4 * kSkinnyFlat];
   int staged = -1;  // member whose weights sW / sB hold
   for (int t = blockIdx.x; t < num_tiles; t += gridDim.x) {
     const GemmTile tile = tiles[t];
@@ -1850,9 +2005,26 @@ __global__ __launch_bounds__(256) void grouped_gemm_skinny_kernel(const DevLinea
     const int count = min(kSkinnyRows, d.M - r0);
     bool pairs = false;
     if constexpr (sizeof(T) == 4) pairs = d.K == 8 && d.N == 8 && d.ldx == 8 && d.ldy == 8 && (d.vec & 3) == 3;
+    // fp32 4 x 2 with aligned rows: each row is one 16-byte load and one 8-byte
+    // store already, both consecutive over the lanes, and the way through LDS
+    // costs more than the wider stores give (two members of 8e6 rows: 71 us
+    // straight, 84 us through LDS)
+    bool whole = false;
+    if constexpr (sizeof(T) == 4) whole = d.K == 4 && d.N == 2 && (d.vec & 1) && ((uintptr_t)d.y & 7) == 0;
     if (pairs)
       skinny_item_pairs<ACT>(d, r0, count, restage, sW, sB);
-    else if (d.K <= 4 && d.N <= 2)
+    else if (d.ldx == d.K && d.ldy == d.N && !whole) {
+      if (d.K <= 4 && d.N <= 2)
+        skinny_item_flat<T, 4, 2, ACT>(d, r0, count, restage, sW, sB, sArea);
+      else if (d.K <= 4 && d.N <= 4)
+        skinny_item_flat<T, 4, 4, ACT>(d, r0, count, restage, sW, sB, sArea);
+      else if (d.K <= 4)
+        skinny_item_flat<T, 4, 8, ACT>(d, r0, count, restage, sW, sB, sArea);
+      else if (d.N <= 4)
+        skinny_item_flat<T, 8, 4, ACT>(d, r0, count, restage, sW, sB, sArea);
+      else
+        skinny_item_flat<T, 8, 8, ACT>(d, r0, count, restage, sW, sB, sArea);
+    } else if (d.K <= 4 && d.N <= 2)
       skinny_item<T, 4, 2, ACT, 8>(d, r0, count, restage, sW, sB);
     else if (d.K <= 4 && d.N <= 4)
       skinny_item<T, 4, 4, ACT, 8>(d, r0, count, restage, sW, sB);

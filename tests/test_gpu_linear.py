@@ -235,6 +235,30 @@ def test_skinny_strided_rows_and_no_bias(dtype):
     _check(ms, ys, dtype, "tanh", f"skinny no bias {dtype}")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("act", ["none", "sigmoid"])
+def test_skinny_contiguous_rows(dtype, act):
+    """Contiguous members of every K and N, at odd element offsets: row counts
+    around a wave's pass, a workgroup's pass and an item, whose runs end inside
+    a 16-byte chunk; the values around each y stay as they are."""
+    say(f"[linear skinny contiguous] {dtype} {act}")
+    counts = [1, 2, 63, 255, 257, 511, 513, 1023, 1025, 2047, 2049, 4097]
+    shapes = [(counts[(5 * k + n) % len(counts)], k, n) for k in range(1, 9) for n in range(1, 9)]
+    ms = _members(shapes, dtype, seed=34)
+    xs, ys, bufs = [], [], []
+    for i, (x, w, _) in enumerate(ms):
+        M, K, N, off = x.shape[0], x.shape[1], w.shape[0], i % 3
+        xb = torch.zeros(M * K + off, dtype=x.dtype, device="cuda")
+        xs.append(xb[off:].view(M, K).copy_(x))
+        yb = torch.full((off + M * N + 9,), 77.0, dtype=x.dtype, device="cuda")
+        ys.append(yb[off:off + M * N].view(M, N))
+        bufs.append((yb, off, off + M * N))
+    B.optimus_grouped_linear(xs, [m[1] for m in ms], [m[2] for m in ms], ys, act)
+    _check(ms, ys, dtype, act, f"skinny contiguous {dtype} {act}")
+    for s, (yb, a, b) in zip(shapes, bufs):
+        assert bool((yb[:a] == 77.0).all()) and bool((yb[b:] == 77.0).all()), f"{s}: wrote beside its rows"
+
+
 def test_skinny_against_tiled_kernel():
     """The same fp32 group through the tiled MFMA kernel (variant 3) and the
     streaming kernel: both against the oracle."""
